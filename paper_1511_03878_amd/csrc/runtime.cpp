@@ -1767,7 +1767,7 @@ void BatchImpl<T>::build_tables()
     maxwell_tile<T>(tile_preset, tx, ty);
     maxP0 = maxP1 = maxP2 = 1;
     int64_t items = 0;
-    int64_t particles = 0;
+    int64_t particles = 0, occupied = 0;  // live particles, patches that hold any
     if (ns > kMaxBatch) throw Error(PIC_EINVAL, "too many simulations in one batch");
     for (int i = 0; i < ns; ++i) {
         SimImpl<T> *m = members[i];
@@ -1781,7 +1781,10 @@ void BatchImpl<T>::build_tables()
         maxP0 = std::max(maxP0, m->P[0]);
         maxP1 = std::max(maxP1, m->P[1]);
         maxP2 = std::max(maxP2, m->P[2]);
-        particles += m->num_particles();
+        for (const int32_t c : m->read_counts()) {
+            particles += c;
+            occupied += c > 0;
+        }
     }
     total_patches = pp[ns];
     total_tiles = tp[ns];
@@ -1800,24 +1803,35 @@ void BatchImpl<T>::build_tables()
                 m->P[0] != members[0]->P[0] || m->P[1] != members[0]->P[1] || m->P[2] != members[0]->P[2])
                 patch_const = 0;
     }
-    // chunk: enough items to fill every CU several times over, at most 4096
-    // particles in 2-D (laser box: 4096 beat 8192 and 16384) and 16384 in 3-D
-    // (blob box: one item per 8^3 patch saves the per-item staging, flush and
-    // deferred-list batches; 22.0 ms per launch against 22.7 ms at 4096)
+    // chunk: four items per CU, but at least 1024 particles (an item pays its
+    // field staging, current flush and barriers once: 128 x 128 box of 16
+    // particles per cell, FP32, 86.8 us per step at 256 particles per item,
+    // 75.3 at 512, 68.8 at 1024, 76.3 at 2048) and at most 4096 in 2-D (laser
+    // box: 4096 beat 8192 and 16384) and 16384 in 3-D (blob box: one item per
+    // 8^3 patch saves the per-item staging, flush and deferred-list batches;
+    // 22.0 ms per launch against 22.7 ms at 4096).  The chunk is then an
+    // eighth above an equal part of the mean occupied patch: a chunk that the
+    // mean divides exactly leaves half of the patches a rest of a few
+    // particles (512 x 512 box of 1024-particle patches: 91.5 us per step at
+    // a chunk of 1024, 88.2 us with whole patches).
     chunk = 0;
     for (auto *m : members) chunk = std::max(chunk, (int)m->desc.chunk);
     if (chunk == 0) {
-        const int64_t target = (int64_t)cu_count() * 8;
-        int64_t c = particles / std::max<int64_t>(target, 1);
-        c = std::max<int64_t>(c, 256);
+        int64_t c = particles / std::max<int64_t>((int64_t)cu_count() * 4, 1);
+        c = std::max<int64_t>(c, 1024);
         c = std::min<int64_t>(c, nd == 3 ? 16384 : 4096);
-        chunk = (int)c;
+        const int64_t mean = particles / std::max<int64_t>(occupied, 1);
+        const int64_t parts = std::max<int64_t>(1, (mean + c / 2) / c);
+        chunk = (int)std::min<int64_t>(std::max<int64_t>(mean / parts * 9 / 8, c), 16384);
     }
     for (auto *m : members) items += m->max_items(chunk);
     items = std::max<int64_t>(items, 1);
     use_graph = false;
     for (auto *m : members) use_graph = use_graph || m->desc.graph;
-    block = (sizeof(T) == 8 && nd == 2) ? 1024 : 512;
+    // 512 threads (2-D FP64, 512 against 1024: 64 x 64 box 55 against 59 us
+    // per step, 512 x 128 laser box 74 against 81, 4096 x 1024 laser box 688
+    // against 698)
+    block = 512;
     for (auto *m : members) if (m->desc.block) block = m->desc.block;
     const int occ = std::max(1, nd == 3 ? particles3d_occupancy<T>(block, maxP0, maxP1, maxP2, patch_const)
                                         : particles_occupancy<T>(block, maxP0, maxP1));
