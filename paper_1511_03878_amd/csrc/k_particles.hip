@@ -20,12 +20,10 @@ namespace pic {
 
 namespace {
 
+// 9-node gather of one component; r: the window's first tile entry.
 template <typename T>
-__device__ __forceinline__ T gather9(const T *tile, int fw, int i0, int j0, const T wx[3],
-                                     const T wy[3])
+__device__ __forceinline__ T gather9(const T *r, int fw, const T wx[3], const T wy[3])
 {
-    // tile entry of node (i, j) is (j + 1) * fw + (i + 1)
-    const T *r = tile + j0 * fw + i0;
     T acc = T(0);
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
@@ -34,6 +32,29 @@ __device__ __forceinline__ T gather9(const T *tile, int fw, int i0, int j0, cons
     }
     return acc;
 }
+
+// ... and of two components on the same nodes, kept as pairs: one LDS read
+// takes both, and its offsets fit the instruction (a tile per component
+// needed an address add for most of its reads).
+template <typename T>
+__device__ __forceinline__ void gather9x2(const Vec2<T> *r, int fw, const T wx[3], const T wy[3], T &a, T &b2)
+{
+    T acc0 = T(0), acc1 = T(0);
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+        const Vec2<T> q0 = r[b * fw], q1 = r[b * fw + 1], q2 = r[b * fw + 2];
+        const T r0 = q0.x * wx[0] + q1.x * wx[1] + q2.x * wx[2];
+        const T r1 = q0.y * wx[0] + q1.y * wx[1] + q2.y * wx[2];
+        acc0 += r0 * wy[b];
+        acc1 += r1 * wy[b];
+    }
+    a = acc0;
+    b2 = acc1;
+}
+
+// 64-bit words of the current tile (an even number: the field pairs after it
+// are up to 16 bytes wide)
+__host__ __device__ constexpr int jtile_words(int jstride) { return (3 * jstride + 1) & ~1; }
 
 // PC > 0: every simulation of the launch has PC x PC-cell patches, so tile
 // strides are compile-time constants and LDS offsets fold into instructions.
@@ -52,17 +73,21 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
     // current tile first (FP64 accumulation for either storage precision:
     // LDS float atomics are much slower here than FP64 ones), then fields
     long long *Jt = reinterpret_cast<long long *>(smem_raw);
-    T *Ft = reinterpret_cast<T *>(Jt + 3 * jstride);
+    // field tile: (Ex, By) pairs, (Ey, Bx) pairs, Ez, Bz (the two components
+    // of a pair sit on the same nodes); entry (j + 1) * fw + (i + 1) is node
+    // (i, j) of the patch
+    Vec2<T> *Fa = reinterpret_cast<Vec2<T> *>(Jt + jtile_words(jstride));
+    Vec2<T> *Fb = Fa + fstride;
+    T *Fz = reinterpret_cast<T *>(Fb + fstride), *Fbz = Fz + fstride;
     __shared__ int s_item[2];
 
     const int tid = threadIdx.x, ln = tid % kWave;
     const int total = *nitems;
-    // Items are claimed one ahead: the next index is requested while the
-    // current item runs and published through the other of two LDS slots.
-    if (tid == 0) s_item[0] = atomicAdd(head, 1);
-    __syncthreads();
-    int idx = __builtin_amdgcn_readfirstlane(s_item[0]);
-    int slot = 1;
+    // Workgroup b starts on item b; further items are claimed one ahead from
+    // a counter: the next index is requested while the current item runs and
+    // published through one of two LDS slots.
+    int idx = blockIdx.x;
+    int slot = 0;
     // Kinetic energy: a running sum per lane, reduced over the wave and
     // added to the simulation's per-patch partials when the wave moves on to
     // another simulation and at the end (partials of different waves land
@@ -76,7 +101,7 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
     };
     while (idx < total) {
         int next = 0;
-        if (tid == 0) next = atomicAdd(head, 1);
+        if (tid == 0) next = (int)gridDim.x + atomicAdd(head, 1);
         const Item it = items[idx];
         const long long t_item = (stamps && tid == 0) ? wall_clock64() : 0;
         const int si = __builtin_amdgcn_readfirstlane(it.x & kItemSimMask);
@@ -135,9 +160,15 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
         const int wv = __builtin_amdgcn_readfirstlane(tid / kWave);
         const int npass = cnt / (kWave * S_), ufull = npass * S_;
         const int uend = ufull + (cnt - npass * kWave * S_ + kWave - 1) / kWave;
+        // (a wave's units are NW apart, so where S divides NW its particle index
+        // advances by 64 per unit number: no division in the loop)
+        const bool even = NW % S_ == 0;
+        const int pfull = kWave * S_ * (wv / S_) + ln * S_ + (wv % S_) - kWave * wv;
+        const int prest = kWave * S_ * npass - kWave * ufull + ln;
         auto unit_particle = [&](int u) {
-            return u < ufull ? kWave * S_ * (u / S_) + ln * S_ + (u % S_)
-                             : kWave * S_ * npass + kWave * (u - ufull) + ln;
+            if (u >= ufull) return prest + kWave * u;
+            if (even) return pfull + kWave * u;
+            return kWave * S_ * (u / S_) + ln * S_ + (u % S_);
         };
         // an item holds at least one particle, so index cnt - 1 is valid
         T nx_, ny_, nux, nuy, nuz, nw_;
@@ -177,9 +208,15 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int t = t0 + r * BLOCK + tid;
-                if (t < fw * fh)
+                T f[6];
 #pragma unroll
-                    for (int c = 0; c < 6; ++c) Ft[c * fstride + t] = ok[r][c] ? v[r][c] : T(0);
+                for (int c = 0; c < 6; ++c) f[c] = ok[r][c] ? v[r][c] : T(0);
+                if (t < fw * fh) {
+                    Fa[t] = Vec2<T>{f[0], f[4]};
+                    Fb[t] = Vec2<T>{f[1], f[3]};
+                    Fz[t] = f[2];
+                    Fbz[t] = f[5];
+                }
             }
         }
         for (int t = tid; t < 3 * jstride; t += BLOCK) Jt[t] = 0;
@@ -204,12 +241,12 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
             qweights(yl - (T)ipy, wpy[0], wpy[1], wpy[2]);
             qweights(yl - (T)idy - T(0.5), wdy[0], wdy[1], wdy[2]);
             // node i0-1 sits at tile column i0, so the window starts at i0
-            const T Ex = gather9(Ft + 0 * fstride, fw, idx_, ipy, wdx, wpy);
-            const T Ey = gather9(Ft + 1 * fstride, fw, ipx, idy, wpx, wdy);
-            const T Ez = gather9(Ft + 2 * fstride, fw, ipx, ipy, wpx, wpy);
-            const T Bx = gather9(Ft + 3 * fstride, fw, ipx, idy, wpx, wdy);
-            const T By = gather9(Ft + 4 * fstride, fw, idx_, ipy, wdx, wpy);
-            const T Bz = gather9(Ft + 5 * fstride, fw, idx_, idy, wdx, wdy);
+            const int rp = __mul24(ipy, fw), rd = __mul24(idy, fw);
+            T Ex, By, Ey, Bx;
+            gather9x2(Fa + (rp + idx_), fw, wdx, wpy, Ex, By);
+            gather9x2(Fb + (rd + ipx), fw, wpx, wdy, Ey, Bx);
+            const T Ez = gather9(Fz + (rp + ipx), fw, wpx, wpy);
+            const T Bz = gather9(Fbz + (rd + idx_), fw, wdx, wdy);
 
             // ---- Boris ------------------------------------------------------
             const T usq0 = ux * ux + uy * uy + uz * uz;
@@ -256,26 +293,28 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                 y1 = yl;
             } else {
                 // ---- Esirkepov deposit on a 4x4 node window ------------------
-                // Only window slot 3 of an axis depends on whether the nearest
-                // node changed; its entries are exactly zero otherwise and their
-                // atomics are skipped (masked lanes cost the LDS nothing).
-                int mx, my;
-                double S0x[4], DSx[4], S0y[4], DSy[4];
-                const bool cx = window4(xl, (double)dxl, mx, S0x, DSx);
-                const bool cy = window4(yl, (double)dyl, my, S0y, DSy);
+                // Window slot 3 of an axis carries weight only when the
+                // nearest node changed on it; its entries sit in blocks of
+                // their own, which a wave without such a lane jumps over.  A
+                // wave of particles at rest skips the windows too.
                 const double qw = (double)wgt;
                 // factors of the current carry the fixed-point scale fs
                 const double az = (double)q * qw * (double)(uz * ig1) * fs;
-                long long *Jxt = Jt, *Jyt = Jt + jstride, *Jzt = Jt + 2 * jstride;
-                const int r0 = (my + 2) * jw + (mx + 2);
-                // time-averaged transverse weights
-                double wx[4], wy[4];
+                const bool inplane = dxl != T(0) || dyl != T(0);
+                if (inplane || az != 0.0) {
+                    int mx, my;
+                    double S0x[4], DSx[4], S0y[4], DSy[4];
+                    const bool cx = window4(xl, (double)dxl, mx, S0x, DSx);
+                    const bool cy = window4(yl, (double)dyl, my, S0y, DSy);
+                    long long *Jxt = Jt + (__mul24(my + 2, jw) + (mx + 2));
+                    long long *Jyt = Jxt + jstride, *Jzt = Jxt + 2 * jstride;
+                    // time-averaged transverse weights
+                    double wx[4], wy[4];
 #pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    wx[k] = S0x[k] + 0.5 * DSx[k];
-                    wy[k] = S0y[k] + 0.5 * DSy[k];
-                }
-                if (dxl != T(0) || dyl != T(0)) {
+                    for (int k = 0; k < 4; ++k) {
+                        wx[k] = S0x[k] + 0.5 * DSx[k];
+                        wy[k] = S0y[k] + 0.5 * DSy[k];
+                    }
                     // Jx on dual x nodes: running sums of -q w (dx/dt) DSx, times wy
                     double px[3], py[3];
                     const double cq = cx_ * qw * fs, dq = cy_ * qw * fs;
@@ -285,31 +324,6 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                     py[0] = dq * DSy[0];
                     py[1] = py[0] + dq * DSy[1];
                     py[2] = py[1] + dq * DSy[2];
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        fix_add_prod(&Jxt[r0 + j * jw + 0], px[0], wy[j]);
-                        fix_add_prod(&Jxt[r0 + j * jw + 1], px[1], wy[j]);
-                        if (cx) fix_add_prod(&Jxt[r0 + j * jw + 2], px[2], wy[j]);
-                    }
-                    if (cy) {
-                        fix_add_prod(&Jxt[r0 + 3 * jw + 0], px[0], wy[3]);
-                        fix_add_prod(&Jxt[r0 + 3 * jw + 1], px[1], wy[3]);
-                        if (cx) fix_add_prod(&Jxt[r0 + 3 * jw + 2], px[2], wy[3]);
-                    }
-                    // Jy on dual y nodes: running sums along y, times wx
-#pragma unroll
-                    for (int i = 0; i < 3; ++i) {
-                        fix_add_prod(&Jyt[r0 + 0 * jw + i], py[0], wx[i]);
-                        fix_add_prod(&Jyt[r0 + 1 * jw + i], py[1], wx[i]);
-                        if (cy) fix_add_prod(&Jyt[r0 + 2 * jw + i], py[2], wx[i]);
-                    }
-                    if (cx) {
-                        fix_add_prod(&Jyt[r0 + 0 * jw + 3], py[0], wx[3]);
-                        fix_add_prod(&Jyt[r0 + 1 * jw + 3], py[1], wx[3]);
-                        if (cy) fix_add_prod(&Jyt[r0 + 2 * jw + 3], py[2], wx[3]);
-                    }
-                }
-                if (az != 0.0) {
                     // Jz = q w vz (S0x S0y + DSx S0y / 2 + S0x DSy / 2 + DSx DSy / 3)
                     //    = q w vz (wx S0y + bx DSy), bx = S0x / 2 + DSx / 3
                     double ax_[4], bx_[4];
@@ -318,18 +332,49 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                         ax_[k] = az * wx[k];
                         bx_[k] = az * (0.5 * S0x[k] + DSx[k] * (1.0 / 3.0));
                     }
+                    if (inplane) {
 #pragma unroll
-                    for (int j = 0; j < 3; ++j) {
+                        for (int j = 0; j < 3; ++j) {
+                            fix_add_prod(&Jxt[j * jw + 0], px[0], wy[j]);
+                            fix_add_prod(&Jxt[j * jw + 1], px[1], wy[j]);
+                        }
+                        // Jy on dual y nodes: running sums along y, times wx
 #pragma unroll
-                        for (int i = 0; i < 3; ++i)
-                            fix_add_2prod(&Jzt[r0 + j * jw + i], ax_[i], S0y[j], bx_[i], DSy[j]);
-                        if (cx) fix_add_2prod(&Jzt[r0 + j * jw + 3], ax_[3], S0y[j], bx_[3], DSy[j]);
+                        for (int i = 0; i < 3; ++i) {
+                            fix_add_prod(&Jyt[0 * jw + i], py[0], wx[i]);
+                            fix_add_prod(&Jyt[1 * jw + i], py[1], wx[i]);
+                        }
+                    }
+                    if (az != 0.0) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j)
+#pragma unroll
+                            for (int i = 0; i < 3; ++i)
+                                fix_add_2prod(&Jzt[j * jw + i], ax_[i], S0y[j], bx_[i], DSy[j]);
+                    }
+                    // (a zero px, py or az adds zero)
+                    if (cx) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j) {
+                            fix_add_prod(&Jxt[j * jw + 2], px[2], wy[j]);
+                            fix_add_2prod(&Jzt[j * jw + 3], ax_[3], S0y[j], bx_[3], DSy[j]);
+                        }
+                        fix_add_prod(&Jyt[0 * jw + 3], py[0], wx[3]);
+                        fix_add_prod(&Jyt[1 * jw + 3], py[1], wx[3]);
                     }
                     if (cy) {
 #pragma unroll
-                        for (int i = 0; i < 3; ++i)
-                            fix_add_2prod(&Jzt[r0 + 3 * jw + i], ax_[i], S0y[3], bx_[i], DSy[3]);
-                        if (cx) fix_add_2prod(&Jzt[r0 + 3 * jw + 3], ax_[3], S0y[3], bx_[3], DSy[3]);
+                        for (int i = 0; i < 3; ++i) {
+                            fix_add_prod(&Jyt[2 * jw + i], py[2], wx[i]);
+                            fix_add_2prod(&Jzt[3 * jw + i], ax_[i], S0y[3], bx_[i], DSy[3]);
+                        }
+                        fix_add_prod(&Jxt[3 * jw + 0], px[0], wy[3]);
+                        fix_add_prod(&Jxt[3 * jw + 1], px[1], wy[3]);
+                        if (cx) {
+                            fix_add_prod(&Jxt[3 * jw + 2], px[2], wy[3]);
+                            fix_add_prod(&Jyt[2 * jw + 3], py[2], wx[3]);
+                            fix_add_2prod(&Jzt[3 * jw + 3], ax_[3], S0y[3], bx_[3], DSy[3]);
+                        }
                     }
                 }
 
@@ -390,7 +435,7 @@ size_t lds_bytes(int maxP0, int maxP1, int &fstride, int &jstride)
 {
     fstride = (maxP0 + 3) * (maxP1 + 3);
     jstride = (maxP0 + 5) * (maxP1 + 5);
-    return sizeof(int64_t) * (size_t)(3 * jstride) + sizeof(T) * (size_t)(6 * fstride);
+    return sizeof(int64_t) * (size_t)jtile_words(jstride) + sizeof(T) * (size_t)(6 * fstride);
 }
 
 }  // namespace

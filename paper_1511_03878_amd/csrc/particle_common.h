@@ -41,10 +41,22 @@ __device__ __forceinline__ bool window4(T xl, double disp, int &m, W S0[4], W DS
     qweights(d1, o1m, o10, o1p);
     int lo = sg < 0 ? sg : 0;
     m = i0 - 1 + lo;
-    bool s0 = lo < 0;   // old support starts at window slot 1
-    bool s1 = sg > 0;   // new support starts at window slot 1
-    double A0[4] = {s0 ? 0.0 : o0m, s0 ? o0m : o00, s0 ? o00 : o0p, s0 ? o0p : 0.0};
-    double A1[4] = {s1 ? 0.0 : o1m, s1 ? o1m : o10, s1 ? o10 : o1p, s1 ? o1p : 0.0};
+    double A0[4] = {o0m, o00, o0p, 0.0};
+    double A1[4] = {o1m, o10, o1p, 0.0};
+    // the shifts between the two supports, jumped over by a wave none of
+    // whose particles changed its nearest node
+    if (__any(sg != 0)) {
+        const bool s0 = lo < 0;   // old support starts at window slot 1
+        const bool s1 = sg > 0;   // new support starts at window slot 1
+        A0[0] = s0 ? 0.0 : o0m;
+        A0[1] = s0 ? o0m : o00;
+        A0[2] = s0 ? o00 : o0p;
+        A0[3] = s0 ? o0p : 0.0;
+        A1[0] = s1 ? 0.0 : o1m;
+        A1[1] = s1 ? o1m : o10;
+        A1[2] = s1 ? o10 : o1p;
+        A1[3] = s1 ? o1p : 0.0;
+    }
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         S0[k] = (W)A0[k];
