@@ -236,7 +236,7 @@ __global__ __launch_bounds__(kYT) void k_maxwell3d_yee(const SimDev<T> *__restri
         const int nbx = (fn0 + kYee3X - 1) / kYee3X, nby = (fn1 + kYee3Y - 1) / kYee3Y;
         // global index of local index 0 along x and y; the block's planes
         const int x0 = (lt % nbx) * kYee3X - 1, y0 = ((lt / nbx) % nby) * kYee3Y - 1;
-        const int zs = (lt / (nbx * nby)) * kYee3Z, ze = min(zs + kYee3Z, fn2);
+        const int zs = (lt / (nbx * nby)) * S.yee_bz, ze = min(zs + S.yee_bz, fn2);
         const int64_t stepn = glb(S.st)->step;
         T *const *Fc = S.F[stepn & 1];
         T *const *Fn = S.F[(stepn + 1) & 1];

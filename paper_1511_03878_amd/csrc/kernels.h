@@ -114,20 +114,31 @@ int particles3d_shape(int P0, int P1, int P2);
 
 // 3-D field update on a periodic box, with the field energy of the incoming
 // E, B per tile.  Yee: one fused kernel over blocks of kYee3X x kYee3Y x
-// kYee3Z nodes, taken plane by plane along z; sixth order: three passes over
+// yee3_planes() nodes, taken plane by plane along z; sixth order: three passes over
 // runs of kMaxwell3dTile nodes.
 // yee / hi_order: the batch holds simulations of that solver.
 template <typename T>
 void launch_maxwell3d(const SimDev<T> *sims, int nsims, const int *tile_prefix, int total_tiles,
                       int grid, bool yee, bool hi_order, hipStream_t st, Ev2 ev = {});
 constexpr int kMaxwell3dTile = 256;
-constexpr int kYee3X = 32, kYee3Y = 8, kYee3Z = 32;
+constexpr int kYee3X = 32, kYee3Y = 8;
+// Planes of a Yee block: 32 on a grid that gives two blocks per CU then, else
+// half as deep until it does, down to 4 (a block's planes follow one another,
+// about 1.7 us each, and two more fill it: 64 x 48 x 40
+// box 57 -> 12 us per launch, 96 x 64 x 64 box, FP64, 77 -> 29).
+inline int yee3_planes(const int fn[3])
+{
+    const int64_t cols = (int64_t)((fn[0] + kYee3X - 1) / kYee3X) * ((fn[1] + kYee3Y - 1) / kYee3Y);
+    int bz = 32;
+    while (bz > 4 && cols * ((fn[2] + bz - 1) / bz) < 512) bz /= 2;
+    return bz;
+}
 // field-update tiles of a 3-D simulation with fn nodes per axis
 inline int64_t maxwell3d_tiles(const int fn[3], int order)
 {
     if (order == 6) return ((int64_t)fn[0] * fn[1] * fn[2] + kMaxwell3dTile - 1) / kMaxwell3dTile;
-    return (int64_t)((fn[0] + kYee3X - 1) / kYee3X) * ((fn[1] + kYee3Y - 1) / kYee3Y) *
-           ((fn[2] + kYee3Z - 1) / kYee3Z);
+    const int bz = yee3_planes(fn);
+    return (int64_t)((fn[0] + kYee3X - 1) / kYee3X) * ((fn[1] + kYee3Y - 1) / kYee3Y) * ((fn[2] + bz - 1) / bz);
 }
 
 // Moving-window jump of one simulation (2-D): a no-op unless the step in

@@ -46,11 +46,14 @@ __device__ __forceinline__ void copy_particle(const SimDev<T> &S, int64_t from, 
 // the staged leavers are queued in a per-wave LDS ring, which is drained 64
 // entries at a time (one lane per particle, so the particle loads of 64
 // leavers are in flight together).
-// threads of the count workgroup: 2-D, and 3-D one wave per patch (about a
-// hundred leavers per 8^3 patch); measured beside the field update, smaller
-// workgroups keep more patches in flight (2-D: 512 and 128 slower than 256)
+// threads of the count workgroup: 256 in 2-D (512 and 128 slower), and in 3-D
+// one wave per patch where the patches fill the chip (about a hundred
+// leavers per 8^3 patch; measured beside the field update, smaller workgroups
+// keep more patches in flight), else 256 (one wave's walk of a patch is then
+// the whole pass: 64 x 48 x 40 box, 240 patches, 85 against 29 us)
 constexpr int kRC = 256;
 constexpr int kRC3 = 64;
+constexpr int kRC3Patches = 2048;
 constexpr int kU = 16;    // 64-slot chunks per batch of code loads (63 VGPRs: 8 waves per SIMD)
 constexpr int kRing = 128;
 

@@ -445,6 +445,7 @@ void SimImpl<T>::refresh_view()
     V.ndim = nd;
     V.lane_stride = lane_stride;
     V.morder = desc.maxwell_order == 6 ? 6 : 2;
+    V.yee_bz = nd == 3 ? yee3_planes(fn) : 0;
     V.win = win_on ? 1 : 0;
     V.wppc[0] = win_ppc[0];
     V.wppc[1] = win_ppc[1];
