@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libpic.so")
 
-SOURCES = ["k_particles.hip", "k_particles3d.hip", "k_maxwell.hip", "k_maxwell3d.hip", "k_rebin.hip",
+SOURCES = ["k_particles.hip", "k_particles3d.hip", "k_maxwell.hip", "k_maxwell3d.hip", "k_rebin.hip", "k_side_by_side.hip",
            "k_window.hip", "k_merge.hip", "k_diag.hip", "k_noalloc.hip", "k_init.hip", "k_current.hip", "runtime.cpp", "order.cpp", "capi.cpp"]
 
 FLAGS = [

@@ -37,184 +37,21 @@ template <typename T, int ND, int NT>
 __global__ __launch_bounds__(NT) void k_rebin_count(const SimDev<T> *__restrict__ sims, int nsims,
                                                     const int *__restrict__ patch_prefix, int total)
 {
-    __shared__ CountSmem<ND, NT / 64> sm;
-    for (int gp = blockIdx.x; gp < total; gp += gridDim.x) {
-        const int s = find_sim(patch_prefix, nsims, gp);
-        const SimDev<T> &S = sims[s];
-        const int p = gp - patch_prefix[s];
-        // the state the patch's count needs, loaded together
-        const uint32_t active = glb(S.st)->active;
-        const int moved = *glb(S.moved + p);
-        const int n = glb(S.count)[p];
-        const int64_t base = glb(S.off)[p];
-        const int key = threadIdx.x < ND ? nb_row<ND>(S.nbt, p)[threadIdx.x] : 0;
-        if (!active) continue;
-        if (!moved) {
-            // no particle of the patch changed patch or was removed: no leavers
-            if (threadIdx.x < ND) glb(S.kcnt)[p * ND + threadIdx.x] = 0;
-            if (threadIdx.x <= ND) glb(S.kofs)[p * (ND + 1) + threadIdx.x] = 0;
-            if (threadIdx.x == 0) glb(S.nleave)[p] = 0;
-            continue;
-        }
-        count_patch<T, ND, NT / 64>(S, p, n, base, key, sm);
-    }
+    rebin_count_patches<T, ND, NT>(sims, nsims, patch_prefix, total, blockIdx.x, gridDim.x);
 }
 
-// Lanes that check one patch: one per possible source (26 or 8), so the
-// counts of all sources are one round of loads instead of a serial walk, and
-// the vacated slots are searched kCheckLanes + 1 parts at a time (64 x 48 x 40
-// box 17 -> 6 us per launch, 4096 x 1024 laser box beside the field update
-// 26 -> 15 us).
-template <int ND>
-constexpr int kCheckLanes = ND == kNDir3 ? 32 : 8;
 template <typename T, int ND>
 __global__ __launch_bounds__(256) void k_rebin_check(const SimDev<T> *__restrict__ sims, int nsims,
                                                      const int *__restrict__ patch_prefix, int total)
 {
-    constexpr int G = kCheckLanes<ND>;
-    const int gp = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G);
-    const int l = threadIdx.x % G;
-    if (gp >= total) return;  // (the whole group)
-    const int s = find_sim(patch_prefix, nsims, gp);
-    const SimDev<T> &S = sims[s];
-    const int q = gp - patch_prefix[s];
-    const gptr_t<const int32_t> row = nb_row<ND>(S.nbt, q);
-    const int i = min(l, ND - 2);  // (always an entry of the row)
-    const uint32_t active = glb(S.st)->active;
-    const int ns = row[ND], src = row[ND + 1 + i], key = row[2 * ND + i];
-    const int n = glb(S.count)[q], L = glb(S.nleave)[q];
-    const gptr_t<const int32_t> h = glb((const int32_t *)S.holes) + glb(S.off)[q];
-    if (!active) return;
-    int A = l < ns ? glb(S.kcnt)[src * ND + key] : 0;
-#pragma unroll
-    for (int o = G / 2; o > 0; o >>= 1) A += __shfl_xor(A, o, G);
-    const int np = n - L + A;
-    // vacated slots below the new count (the list is ascending)
-    int lo = 0, hi = L;
-    while (lo < hi) {
-        auto probe = [&](int j) { return lo + (int)((int64_t)(hi - lo) * (j + 1) / (G + 1)); };
-        const uint64_t below = __ballot(h[probe(l)] < np) >> (threadIdx.x & 63 & ~(G - 1));
-        const int c = __popcll(below & ((1ull << G) - 1));
-        const int lo2 = c > 0 ? probe(c - 1) + 1 : lo;
-        hi = c < G ? probe(c) : hi;
-        lo = lo2;
-    }
-    if (l != 0) return;
-    glb(S.newcount)[q] = np;
-    glb(S.narrive)[q] = A;
-    glb(S.nhole)[q] = lo;
-    if (np > glb(S.cap)[q])
-        __hip_atomic_fetch_or(&glb(S.st)->flags, kFlagPending, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    rebin_check_patches<T, ND>(sims, nsims, patch_prefix, total, blockIdx.x);
 }
 
 template <typename T, int ND, int NT>
 __global__ __launch_bounds__(NT) void k_rebin_scatter(const SimDev<T> *__restrict__ sims, int nsims,
-                                                       const int *__restrict__ patch_prefix,
-                                                       int total)
+                                                      const int *__restrict__ patch_prefix, int total)
 {
-    constexpr int NS = ND - 1;  // at most this many distinct source patches
-    constexpr int kNW = NT / 64;
-    static_assert(NT >= 64 + ND, "threads 64 .. 64 + ND hold the direction keys");
-    __shared__ int s_scnt[NS];
-    __shared__ int64_t s_sbase[NS];
-    __shared__ int s_ns;
-    __shared__ int s_key[ND];
-    __shared__ int s_wc[kNW];
-    __shared__ int s_run;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-
-    for (int gp = blockIdx.x; gp < total; gp += gridDim.x) {
-        const int s = find_sim(patch_prefix, nsims, gp);
-        const SimDev<T> &S = sims[s];
-        const int q = gp - patch_prefix[s];
-        // everything that depends on q alone, loaded together: the state,
-        // the patch's counts, and per thread one entry of its neighbour row
-        // (threads below NS: a source and its key; threads 64 .. 64 + ND: a
-        // direction's key)
-        const uint32_t active = glb(S.st)->active, flags = glb(S.st)->flags;
-        const int n = glb(S.count)[q], np = glb(S.newcount)[q], nH = glb(S.nhole)[q], A = glb(S.narrive)[q];
-        const int L = glb(S.nleave)[q], nstaged = glb(S.kofs)[q * (ND + 1) + ND];
-        const int64_t base = glb(S.off)[q];
-        const gptr_t<const int32_t> row = nb_row<ND>(S.nbt, q);
-        int r_ns = 0, r_a = 0, r_b = 0;
-        if (tid < NS) {
-            r_ns = row[ND];
-            r_a = row[ND + 1 + tid];
-            r_b = row[2 * ND + tid];
-        } else if (tid >= 64 && tid < 64 + ND) {
-            r_a = row[tid - 64];
-        }
-        if (!active || (flags & kFlagPending)) continue;
-        if (A == 0 && np == n && L == 0) {
-            // nothing arrives and nothing leaves
-            if (tid == 0) {
-                if (q == 0) glb(S.st)->rebinned = 1u;
-                *glb(S.moved + q) = 0;
-            }
-            continue;
-        }
-        if (tid < NS) {
-            // one thread per source: its count and staging base for this patch
-            if (tid < r_ns) {
-                const int sp = r_a, k = r_b;
-                s_scnt[tid] = glb(S.kcnt)[sp * ND + k];
-                s_sbase[tid] = glb(S.off)[sp] + glb(S.kofs)[sp * (ND + 1) + k];
-            }
-            if (tid == 0) {
-                s_ns = r_ns;
-                s_run = 0;
-                if (q == 0) glb(S.st)->rebinned = 1u;
-            }
-        } else if (tid >= 64 && tid < 64 + ND) {
-            s_key[tid - 64] = r_a;
-        }
-        __syncthreads();
-        // arrivals (sources in ascending id, each in its slot order): holes
-        // first, then appended from slot n; one thread per arrival, so the
-        // copies of all sources are in flight together
-        for (int a = tid; a < A; a += NT) {
-            int i = 0, a0 = 0;
-            while (i + 1 < s_ns && a >= a0 + s_scnt[i]) a0 += s_scnt[i++];
-            const int target = a < nH ? glb(S.holes)[base + a] : n + (a - nH);
-            copy_particle(S, s_sbase[i] + (a - a0), base + target, true, false);
-        }
-        // stayers in [n', n) fill the remaining holes
-        if (np < n) {
-            for (int c0 = np; c0 < n; c0 += NT) {
-                const int k = c0 + tid;
-                bool stay = false;
-                if (k < n) {
-                    const uint8_t c = glb(S.code)[base + k];
-                    stay = c != kRemoved && s_key[c] < 0;
-                }
-                const uint64_t b = __ballot(stay);
-                if (lane == 0) s_wc[wave] = __popcll(b);
-                __syncthreads();
-                if (stay) {
-                    int r = s_run + __popcll(b & lt);
-                    for (int w = 0; w < wave; ++w) r += s_wc[w];
-                    copy_particle(S, base + k, base + glb(S.holes)[base + A + r], false, false);
-                }
-                __syncthreads();
-                if (tid == 0) {
-                    int add = 0;
-                    for (int w = 0; w < kNW; ++w) add += s_wc[w];
-                    s_run += add;
-                }
-                __syncthreads();
-            }
-        }
-        if (tid == 0) {
-            glb(S.count)[q] = np;
-            *glb(S.moved + q) = 0;
-            const int removed = L - nstaged;
-            if (removed)
-                __hip_atomic_fetch_add(&glb(S.st)->removed, (uint64_t)removed, __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __syncthreads();
-    }
+    rebin_scatter_patches<T, ND, NT>(sims, nsims, patch_prefix, total, blockIdx.x, gridDim.x);
 }
 
 // ---- step close and work queue --------------------------------------------------
@@ -275,13 +112,35 @@ __global__ __launch_bounds__(kQB) void k_close_queue(const SimDev<T> *__restrict
     __shared__ uint8_t s_par[kMaxBatch];   // parity of the step the queue is for
     __shared__ int s_pushed[kMaxBatch];
     __shared__ int s_pp[kMaxBatch + 1];  // patch prefix of the batch
-    __shared__ int s_cnt[kCntCache];     // particle counts at the first kCntCache queue positions
+    __shared__ int s_cnt[kCntCache];     // particle counts at the queue positions
     __shared__ int s_off[kCntCache];     // and their first particle slots
     __shared__ int s_wsum[kQW];
     __shared__ double s_red[kQW][2];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int nsims = qa.nsims;
+    const bool grid_queue = qa.total_patches > kCntCache;
+    for (int i = tid; i <= nsims; i += kQB) s_pp[i] = qa.patch_prefix[i];
+    __syncthreads();
+
+    // The particle counts and first slots of every queue position are loaded
+    // before the steps are closed (which does not change them), so their
+    // latency overlaps that of the energies and states: the kernel is a chain
+    // of such round trips (128 x 128 box 8.3 -> 7.7 us per launch).
+    constexpr int kPer = kCntCache / kQB;
+    int pc[kPer], po[kPer], ps[kPer];
+#pragma unroll
+    for (int r = 0; r < kPer; ++r) {
+        const int gp = r * kQB + tid;
+        pc[r] = po[r] = ps[r] = 0;
+        if (!grid_queue && gp < qa.total_patches) {
+            const int s = find_sim(s_pp, nsims, gp);
+            const int p = queue_patch(sims, s_pp, gp, s);
+            ps[r] = s;
+            pc[r] = glb((const int32_t *)sims[s].count)[p];
+            po[r] = (int)glb((const int64_t *)sims[s].off)[p];
+        }
+    }
 
     // ---- phase A: close steps, decide participation -------------------------------
     // G waves work on one simulation (all 16 for a single simulation, one each
@@ -293,26 +152,29 @@ __global__ __launch_bounds__(kQB) void k_close_queue(const SimDev<T> *__restrict
     for (int r0 = 0; r0 < nsims; r0 += per_round) {
         const int s = r0 + wave / G;
         bool closing = false;
-        int64_t left = 0;
+        int64_t left = 0, stepn = 0, pushed = 0, removed = 0;
         uint32_t flags = 0;
         if (s < nsims) {
             const SimDev<T> &S = sims[s];
             const gptr_t<SimState> st = glb(S.st);
             flags = st->flags;
             left = st->steps_left;
-            closing = st->active && st->rebinned && !(flags & kFlagPending);
+            stepn = st->step;
+            pushed = st->pushed;
+            removed = st->removed;
+            const uint32_t active = st->active, rebinned = st->rebinned;
+            const int nt = qa.tile_prefix[s + 1] - qa.tile_prefix[s];
+            const gptr_t<const double> up = glb((const double *)S.upart);
+            const gptr_t<double> kp = glb(S.kpart);
             double u = 0.0, k = 0.0;
+            // (summed also where the step is not closed: the sums are then dropped)
+#pragma unroll 8
+            for (int i = sub * 64 + lane; i < nt; i += G * 64) u += up[i];
+#pragma unroll 8
+            for (int i = sub * 64 + lane; i < S.npatch; i += G * 64) k += kp[i];
+            closing = active && rebinned && !(flags & kFlagPending);
             if (closing) {
-                const int nt = qa.tile_prefix[s + 1] - qa.tile_prefix[s];
-                const gptr_t<const double> up = glb((const double *)S.upart);
-                const gptr_t<double> kp = glb(S.kpart);
-#pragma unroll 8
-                for (int i = sub * 64 + lane; i < nt; i += G * 64) u += up[i];
-#pragma unroll 8
-                for (int i = sub * 64 + lane; i < S.npatch; i += G * 64) {
-                    k += kp[i];
-                    kp[i] = 0.0;
-                }
+                for (int i = sub * 64 + lane; i < S.npatch; i += G * 64) kp[i] = 0.0;
 #pragma unroll
                 for (int o = 32; o > 0; o >>= 1) {
                     u += __shfl_xor(u, o, 64);
@@ -329,12 +191,11 @@ __global__ __launch_bounds__(kQB) void k_close_queue(const SimDev<T> *__restrict
                 double u = 0.0, k = 0.0;
                 for (int w = wave; w < wave + G; ++w) { u += s_red[w][0]; k += s_red[w][1]; }
                 if (left > 0) left -= 1;
-                const int64_t n = st->step;
-                gptr_t<double> h = glb(S.hist) + (n % kHistLen) * 4;
+                gptr_t<double> h = glb(S.hist) + (stepn % kHistLen) * 4;
                 h[0] = u;
                 h[1] = k;
-                h[2] = (double)st->pushed;
-                h[3] = (double)st->removed;
+                h[2] = (double)pushed;
+                h[3] = (double)removed;
                 st->U = u;
                 st->K = k;
                 if (st->wpend) {
@@ -344,19 +205,19 @@ __global__ __launch_bounds__(kQB) void k_close_queue(const SimDev<T> *__restrict
                     st->wadd = 0;
                     st->wpend = 0u;
                 }
-                st->step = n + 1;
+                st->step = ++stepn;
                 st->steps_left = left;
                 st->rebinned = 0u;
             }
             const uint32_t act = left > 0 && !(flags & (kFlagPending | kFlagErrMask));
             st->active = act;
             s_act[s] = (uint8_t)act;
-            s_par[s] = (uint8_t)(st->step & 1);
+            s_par[s] = (uint8_t)(stepn & 1);
             s_pushed[s] = 0;
         }
         __syncthreads();
     }
-    if (qa.total_patches > kCntCache) {
+    if (grid_queue) {
         // the grid kernels build the queue: clear their bucket counts and
         // cursors and the pushed counters they add to, and hand them each
         // simulation's participation and step parity
@@ -369,43 +230,19 @@ __global__ __launch_bounds__(kQB) void k_close_queue(const SimDev<T> *__restrict
         return;
     }
     for (int b = tid; b < kBuckets; b += kQB) s_hist[b] = 0;
-    for (int i = tid; i <= nsims; i += kQB) s_pp[i] = qa.patch_prefix[i];
-    __syncthreads();
-
     auto patch_at = [&](int gp, int s) { return queue_patch(sims, s_pp, gp, s); };
-    // ---- particle counts of the first kCntCache patches, loaded together ----------
+    // ---- particle counts of the queue positions (0 where the simulation rests) ---
     const int total = s_pp[nsims];
-    const int ncache = min(total, kCntCache);
-    for (int g0 = 0; g0 < ncache; g0 += 8 * kQB) {
-        int v[8], o[8];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int gp = g0 + r * kQB + tid;
-            v[r] = 0;
-            o[r] = 0;
-            if (gp < ncache) {
-                const int s = find_sim(s_pp, nsims, gp);
-                if (s_act[s]) {
-                    const int p = patch_at(gp, s);
-                    v[r] = glb((const int32_t *)sims[s].count)[p];
-                    o[r] = (int)glb((const int64_t *)sims[s].off)[p];
-                }
-            }
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-            const int gp = g0 + r * kQB + tid;
-            if (gp < ncache) {
-                s_cnt[gp] = v[r];
-                s_off[gp] = o[r];
-            }
+    for (int r = 0; r < kPer; ++r) {
+        const int gp = r * kQB + tid;
+        if (gp < total) {
+            s_cnt[gp] = s_act[ps[r]] ? pc[r] : 0;
+            s_off[gp] = po[r];
         }
     }
     __syncthreads();
-    auto count_of = [&](int gp, int s) {
-        if (gp < kCntCache) return s_cnt[gp];
-        return s_act[s] ? glb((const int32_t *)sims[s].count)[patch_at(gp, s)] : 0;
-    };
+    auto count_of = [&](int gp, int) { return s_cnt[gp]; };
 
     // ---- phase B: chunk histogram (bucket 0 = largest chunks) ------------------------
     // A patch of n particles gives n / chunk full chunks (bucket 0) and one
@@ -479,7 +316,7 @@ __global__ __launch_bounds__(kQB) void k_close_queue(const SimDev<T> *__restrict
         int fbase = 0;
         if (lane == 0 && fsum) fbase = atomicAdd(&s_hist[0], fsum);
         fbase = __shfl(fbase, 0, 64) + incl_f - nfull;
-        const int64_t o = n == 0 ? 0 : gp < kCntCache ? s_off[gp] : glb((const int64_t *)sims[s].off)[p];
+        const int64_t o = n == 0 ? 0 : s_off[gp];
         for (int k = 0; k < nfull; ++k) put(fbase + k, s, p, o + (int64_t)k * chunk, chunk);
         if (rem) put(atomicAdd(&s_hist[bucket(rem)], 1), s, p, o + (int64_t)nfull * chunk, rem);
     }
@@ -685,6 +522,25 @@ void launch_close_queue(const SimDev<T> *sims, const QueueArgs &q, hipStream_t s
 }
 
 template <typename T, int ND>
+static void launch_rebin_rest_nd(const SimDev<T> *sims, int nsims, const int *patch_prefix, int total_patches,
+                                 int grid, hipStream_t st, Ev2 ev)
+{
+    const int64_t lanes = (int64_t)total_patches * kCheckLanes<ND>;
+    hipLaunchKernelGGL((k_rebin_check<T, ND>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, sims,
+                       nsims, patch_prefix, total_patches);
+    hipExtLaunchKernelGGL((k_rebin_scatter<T, ND, kRB>), dim3(grid), dim3(kRB), 0, st, nullptr, ev.stop, 0,
+                          sims, nsims, patch_prefix, total_patches);
+}
+
+template <typename T>
+void launch_rebin_rest(const SimDev<T> *sims, int nsims, const int *patch_prefix, int total_patches, int grid,
+                       int ndim, hipStream_t st)
+{
+    if (ndim == 3) launch_rebin_rest_nd<T, kNDir3>(sims, nsims, patch_prefix, total_patches, grid, st, {});
+    else launch_rebin_rest_nd<T, kNDir2>(sims, nsims, patch_prefix, total_patches, grid, st, {});
+}
+
+template <typename T, int ND>
 static void launch_rebin_nd(const SimDev<T> *sims, int nsims, const int *patch_prefix,
                             int total_patches, int grid, hipStream_t st, Ev2 ev)
 {
@@ -696,11 +552,7 @@ static void launch_rebin_nd(const SimDev<T> *sims, int nsims, const int *patch_p
     else
         hipExtLaunchKernelGGL((k_rebin_count<T, ND, kRC>), cgrid, dim3(kRC), 0, st, ev.start, nullptr, 0,
                               sims, nsims, patch_prefix, total_patches);
-    const int64_t lanes = (int64_t)total_patches * kCheckLanes<ND>;
-    hipLaunchKernelGGL((k_rebin_check<T, ND>), dim3((unsigned)((lanes + 255) / 256)), dim3(256), 0, st, sims,
-                       nsims, patch_prefix, total_patches);
-    hipExtLaunchKernelGGL((k_rebin_scatter<T, ND, kRB>), dim3(grid), dim3(kRB), 0, st, nullptr, ev.stop, 0,
-                          sims, nsims, patch_prefix, total_patches);
+    launch_rebin_rest_nd<T, ND>(sims, nsims, patch_prefix, total_patches, grid, st, ev);
 }
 
 template <typename T>
@@ -730,6 +582,8 @@ void launch_scatter_codes(const uint8_t *packed, const int64_t *packed_off, cons
     template void launch_close_queue<T>(const SimDev<T> *, const QueueArgs &, hipStream_t, Ev2); \
     template void launch_rebin<T>(const SimDev<T> *, int, const int *, int, int, int,            \
                                   hipStream_t, Ev2);                                             \
+    template void launch_rebin_rest<T>(const SimDev<T> *, int, const int *, int, int, int,       \
+                                       hipStream_t);                                             \
     template void launch_relayout<T>(const SimDev<T> *, const SimDev<T> *, int, hipStream_t);
 PIC_INST(float)
 PIC_INST(double)

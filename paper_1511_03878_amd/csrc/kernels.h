@@ -170,6 +170,19 @@ template <typename T>
 void launch_rebin(const SimDev<T> *sims, int nsims, const int *patch_prefix, int total_patches,
                   int grid, int ndim, hipStream_t st, Ev2 ev = {});
 
+// The check and scatter passes alone (after a count pass).
+template <typename T>
+void launch_rebin_rest(const SimDev<T> *sims, int nsims, const int *patch_prefix, int total_patches, int grid,
+                       int ndim, hipStream_t st);
+
+// Field update and re-binning in shared launches (k_side_by_side.hip) on one
+// stream; every simulation of the batch uses the same solver and 2-D tiles
+// have the default shape.
+template <typename T>
+void launch_fields_rebin(const SimDev<T> *sims, int nsims, const int *tile_prefix, int tiles, int field_wgs,
+                         const int *patch_prefix, int patches, int rebin_grid, int ndim, bool hi_order,
+                         hipStream_t st);
+
 // Copy particles into a new per-patch layout (capacity growth).
 template <typename T>
 void launch_relayout(const SimDev<T> *src, const SimDev<T> *dst, int npatch, hipStream_t st);

@@ -1,5 +1,5 @@
-// Re-binning helpers: neighbour-table rows, particle copies and the
-// per-patch leaver count of the re-binning kernels.
+// Re-binning: neighbour-table rows, particle copies and the bodies of its
+// three passes (described in k_rebin.hip).
 #pragma once
 
 #include "pic_dev.h"
@@ -214,6 +214,194 @@ __device__ __forceinline__ void count_patch(const SimDev<T> &S, int p, int n, in
         }
     }
     group_sync();
+}
+
+// Count pass over the patches of workgroup wg of nwg (NT threads).
+template <typename T, int ND, int NT>
+__device__ __forceinline__ void rebin_count_patches(const SimDev<T> *__restrict__ sims, int nsims,
+                                                    const int *__restrict__ patch_prefix, int total, int wg,
+                                                    int nwg)
+{
+    __shared__ CountSmem<ND, NT / 64> sm;
+    for (int gp = wg; gp < total; gp += nwg) {
+        const int s = find_sim(patch_prefix, nsims, gp);
+        const SimDev<T> &S = sims[s];
+        const int p = gp - patch_prefix[s];
+        // the state the patch's count needs, loaded together
+        const uint32_t active = glb(S.st)->active;
+        const int moved = *glb(S.moved + p);
+        const int n = glb(S.count)[p];
+        const int64_t base = glb(S.off)[p];
+        const int key = threadIdx.x < ND ? nb_row<ND>(S.nbt, p)[threadIdx.x] : 0;
+        if (!active) continue;
+        if (!moved) {
+            // no particle of the patch changed patch or was removed: no leavers
+            if (threadIdx.x < ND) glb(S.kcnt)[p * ND + threadIdx.x] = 0;
+            if (threadIdx.x <= ND) glb(S.kofs)[p * (ND + 1) + threadIdx.x] = 0;
+            if (threadIdx.x == 0) glb(S.nleave)[p] = 0;
+            continue;
+        }
+        count_patch<T, ND, NT / 64>(S, p, n, base, key, sm);
+    }
+}
+
+// Lanes that check one patch: one per possible source (26 or 8), so the
+// counts of all sources are one round of loads instead of a serial walk, and
+// the vacated slots are searched kCheckLanes + 1 parts at a time (64 x 48 x 40
+// box 17 -> 6 us per launch, 4096 x 1024 laser box beside the field update
+// 26 -> 15 us).
+template <int ND>
+constexpr int kCheckLanes = ND == kNDir3 ? 32 : 8;
+// Check pass of one patch (wg: workgroup of 256 threads).
+template <typename T, int ND>
+__device__ __forceinline__ void rebin_check_patches(const SimDev<T> *__restrict__ sims, int nsims,
+                                                    const int *__restrict__ patch_prefix, int total, int wg)
+{
+    constexpr int G = kCheckLanes<ND>;
+    const int gp = (int)((wg * (int64_t)256 + threadIdx.x) / G);
+    const int l = threadIdx.x % G;
+    if (gp >= total) return;  // (the whole group)
+    const int s = find_sim(patch_prefix, nsims, gp);
+    const SimDev<T> &S = sims[s];
+    const int q = gp - patch_prefix[s];
+    const gptr_t<const int32_t> row = nb_row<ND>(S.nbt, q);
+    const int i = min(l, ND - 2);  // (always an entry of the row)
+    const uint32_t active = glb(S.st)->active;
+    const int ns = row[ND], src = row[ND + 1 + i], key = row[2 * ND + i];
+    const int n = glb(S.count)[q], L = glb(S.nleave)[q];
+    const gptr_t<const int32_t> h = glb((const int32_t *)S.holes) + glb(S.off)[q];
+    if (!active) return;
+    int A = l < ns ? glb(S.kcnt)[src * ND + key] : 0;
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) A += __shfl_xor(A, o, G);
+    const int np = n - L + A;
+    // vacated slots below the new count (the list is ascending)
+    int lo = 0, hi = L;
+    while (lo < hi) {
+        auto probe = [&](int j) { return lo + (int)((int64_t)(hi - lo) * (j + 1) / (G + 1)); };
+        const uint64_t below = __ballot(h[probe(l)] < np) >> (threadIdx.x & 63 & ~(G - 1));
+        const int c = __popcll(below & ((1ull << G) - 1));
+        const int lo2 = c > 0 ? probe(c - 1) + 1 : lo;
+        hi = c < G ? probe(c) : hi;
+        lo = lo2;
+    }
+    if (l != 0) return;
+    glb(S.newcount)[q] = np;
+    glb(S.narrive)[q] = A;
+    glb(S.nhole)[q] = lo;
+    if (np > glb(S.cap)[q])
+        __hip_atomic_fetch_or(&glb(S.st)->flags, kFlagPending, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Scatter pass over the patches of workgroup wg of nwg (NT threads).
+template <typename T, int ND, int NT>
+__device__ __forceinline__ void rebin_scatter_patches(const SimDev<T> *__restrict__ sims, int nsims,
+                                                      const int *__restrict__ patch_prefix, int total, int wg,
+                                                      int nwg)
+{
+    constexpr int NS = ND - 1;  // at most this many distinct source patches
+    constexpr int kNW = NT / 64;
+    static_assert(NT >= 64 + ND, "threads 64 .. 64 + ND hold the direction keys");
+    __shared__ int s_scnt[NS];
+    __shared__ int64_t s_sbase[NS];
+    __shared__ int s_ns;
+    __shared__ int s_key[ND];
+    __shared__ int s_wc[kNW];
+    __shared__ int s_run;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+
+    for (int gp = wg; gp < total; gp += nwg) {
+        const int s = find_sim(patch_prefix, nsims, gp);
+        const SimDev<T> &S = sims[s];
+        const int q = gp - patch_prefix[s];
+        // everything that depends on q alone, loaded together: the state,
+        // the patch's counts, and per thread one entry of its neighbour row
+        // (threads below NS: a source and its key; threads 64 .. 64 + ND: a
+        // direction's key)
+        const uint32_t active = glb(S.st)->active, flags = glb(S.st)->flags;
+        const int n = glb(S.count)[q], np = glb(S.newcount)[q], nH = glb(S.nhole)[q], A = glb(S.narrive)[q];
+        const int L = glb(S.nleave)[q], nstaged = glb(S.kofs)[q * (ND + 1) + ND];
+        const int64_t base = glb(S.off)[q];
+        const gptr_t<const int32_t> row = nb_row<ND>(S.nbt, q);
+        int r_ns = 0, r_a = 0, r_b = 0;
+        if (tid < NS) {
+            r_ns = row[ND];
+            r_a = row[ND + 1 + tid];
+            r_b = row[2 * ND + tid];
+        } else if (tid >= 64 && tid < 64 + ND) {
+            r_a = row[tid - 64];
+        }
+        if (!active || (flags & kFlagPending)) continue;
+        if (A == 0 && np == n && L == 0) {
+            // nothing arrives and nothing leaves
+            if (tid == 0) {
+                if (q == 0) glb(S.st)->rebinned = 1u;
+                *glb(S.moved + q) = 0;
+            }
+            continue;
+        }
+        if (tid < NS) {
+            // one thread per source: its count and staging base for this patch
+            if (tid < r_ns) {
+                const int sp = r_a, k = r_b;
+                s_scnt[tid] = glb(S.kcnt)[sp * ND + k];
+                s_sbase[tid] = glb(S.off)[sp] + glb(S.kofs)[sp * (ND + 1) + k];
+            }
+            if (tid == 0) {
+                s_ns = r_ns;
+                s_run = 0;
+                if (q == 0) glb(S.st)->rebinned = 1u;
+            }
+        } else if (tid >= 64 && tid < 64 + ND) {
+            s_key[tid - 64] = r_a;
+        }
+        __syncthreads();
+        // arrivals (sources in ascending id, each in its slot order): holes
+        // first, then appended from slot n; one thread per arrival, so the
+        // copies of all sources are in flight together
+        for (int a = tid; a < A; a += NT) {
+            int i = 0, a0 = 0;
+            while (i + 1 < s_ns && a >= a0 + s_scnt[i]) a0 += s_scnt[i++];
+            const int target = a < nH ? glb(S.holes)[base + a] : n + (a - nH);
+            copy_particle(S, s_sbase[i] + (a - a0), base + target, true, false);
+        }
+        // stayers in [n', n) fill the remaining holes
+        if (np < n) {
+            for (int c0 = np; c0 < n; c0 += NT) {
+                const int k = c0 + tid;
+                bool stay = false;
+                if (k < n) {
+                    const uint8_t c = glb(S.code)[base + k];
+                    stay = c != kRemoved && s_key[c] < 0;
+                }
+                const uint64_t b = __ballot(stay);
+                if (lane == 0) s_wc[wave] = __popcll(b);
+                __syncthreads();
+                if (stay) {
+                    int r = s_run + __popcll(b & lt);
+                    for (int w = 0; w < wave; ++w) r += s_wc[w];
+                    copy_particle(S, base + k, base + glb(S.holes)[base + A + r], false, false);
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    int add = 0;
+                    for (int w = 0; w < kNW; ++w) add += s_wc[w];
+                    s_run += add;
+                }
+                __syncthreads();
+            }
+        }
+        if (tid == 0) {
+            glb(S.count)[q] = np;
+            *glb(S.moved + q) = 0;
+            const int removed = L - nstaged;
+            if (removed)
+                __hip_atomic_fetch_add(&glb(S.st)->removed, (uint64_t)removed, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+    }
 }
 
 }  // namespace pic

@@ -63,6 +63,9 @@ void hipcheck(hipError_t e, const char *what)
     }
 }
 
+// Field nodes up to which a batch counts as small (BatchImpl::build_tables).
+static constexpr int64_t kSideBySideNodes = 3 << 18;
+
 static int cu_count()
 {
     static int cached = 0;
@@ -1769,6 +1772,7 @@ void BatchImpl<T>::build_tables()
     maxP0 = maxP1 = maxP2 = 1;
     int64_t items = 0;
     int64_t particles = 0, occupied = 0;  // live particles, patches that hold any
+    int64_t nodes = 0;                    // field nodes
     if (ns > kMaxBatch) throw Error(PIC_EINVAL, "too many simulations in one batch");
     for (int i = 0; i < ns; ++i) {
         SimImpl<T> *m = members[i];
@@ -1782,6 +1786,7 @@ void BatchImpl<T>::build_tables()
         maxP0 = std::max(maxP0, m->P[0]);
         maxP1 = std::max(maxP1, m->P[1]);
         maxP2 = std::max(maxP2, m->P[2]);
+        nodes += m->fsize;
         for (const int32_t c : m->read_counts()) {
             particles += c;
             occupied += c > 0;
@@ -1839,6 +1844,14 @@ void BatchImpl<T>::build_tables()
     grid_particles = cu_count() * occ;
     grid_maxwell = std::max(1, std::min(total_tiles, cu_count() * (nd == 3 ? 32 : 8)));
     grid_rebin = std::max(1, std::min(total_patches, cu_count() * 8));
+    // Small batches run the field update beside the re-binning in shared
+    // launches instead of on a second stream, whose fork and join take about
+    // 13 us (two streams against shared launches, us per step: 64 x 64 box
+    // 51.5 / 41.1, 128 x 128 58.6 / 49.3, 1536 x 384 laser box 107.2 / 105.5,
+    // 96 x 64 x 64 448 / 448; 1024 x 1024 box 441 / 466, 256 x 128 x 128
+    // 2285 / 2350, where the check and scatter passes would wait for the
+    // field update).
+    side_by_side = !(yee_any && hi_order) && tile_preset == 0 && total_patches <= 2048 && nodes <= kSideBySideNodes;
     if (std::getenv("PIC_LOG"))
         std::fprintf(stderr,
                      "[pic] batch of %d: %d patches, %lld items of <= %d particles, particle kernel "
@@ -1962,7 +1975,15 @@ void BatchImpl<T>::launch_one_step()
     // deterministic members: fixed-point accumulators -> J[step & 1]
     if (ndet) launch_jfix<T>(sims_d, det_list_d, det_prefix_d, ndet, det_nodes, stream);
     // the field update (fields, currents, tile energies) and the re-binning
-    // (particles, counts) touch disjoint data: run them side by side
+    // (particles, counts) touch disjoint data: run them side by side, in one
+    // launch (small batches, unless every kernel group is timed) or on two
+    // streams
+    if (side_by_side && !(tm.enabled && tm.only < 0)) {
+        launch_fields_rebin<T>(sims_d, ns, tile_prefix_d, total_tiles, grid_maxwell, patch_prefix_d, total_patches,
+                               grid_rebin, nd, hi_order, stream);
+        launch_close_queue_pass();
+        return;
+    }
     const bool fork = ensure_side();
     hipStream_t fs = stream;
     if (fork) {

@@ -244,6 +244,7 @@ struct BatchImpl : BatchBase {
     int chunk = 256, block = 256, tile_preset = 0, patch_const = 0;
     bool hi_order = false;  // some member uses the sixth-order field solver
     bool yee_any = true;    // some member uses the Yee solver
+    bool side_by_side = false;  // field update and re-binning share launches (small batches)
     int grid_particles = 1, grid_maxwell = 1, grid_rebin = 1;
     Timing own_timing;
     // step batches replayed from a captured graph
