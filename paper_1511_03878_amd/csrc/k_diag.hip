@@ -4,8 +4,9 @@
 //
 // rho[node] = q sum_p w_p prod_a S2(xi_p,a - node_a) with the quadratic
 // B-spline S2 (the charge assignment that goes with the quadratic gather);
-// it is accumulated in FP64 with device-scope atomics into a caller-given
-// array of fn[0] fn[1] fn[2] doubles that the caller has cleared.
+// it is accumulated in FP64, per patch in LDS and then with device-scope
+// atomics, into a caller-given array of fn[0] fn[1] fn[2] doubles that the
+// caller has cleared.
 //
 // Residuals (evaluated in FP64 at primal nodes, with J on E's staggered
 // positions so that div J and div E sit on primal nodes):
@@ -36,42 +37,60 @@ __device__ __forceinline__ void sweights(double d, double w[3])
     w[2] = 0.5 * (0.5 + d) * (0.5 + d);
 }
 
-// One workgroup per patch; every particle adds its 3^ND node charges.
+// One workgroup per patch.  Every particle adds its 3^ND node charges to an
+// FP64 tile of the patch's nodes (-1 .. P + 1 on every axis) in LDS, and each
+// touched node of the tile is added to `out` once: device-scope atomics for
+// every particle and node kept the pass at their rate (96 x 64 x 64 box of
+// 4.2e6 FP64 particles 3.28 -> 0.1 ms).
 template <typename T, int ND>
-__global__ void k_rho(const SimDev<T> *__restrict__ S, double *__restrict__ out)
+__global__ __launch_bounds__(256) void k_rho(const SimDev<T> *__restrict__ S, double *__restrict__ out)
 {
-    const int p = blockIdx.x;
+    extern __shared__ double tile[];
+    const int p = blockIdx.x, tid = threadIdx.x;
     const int n = S->count[p];
+    if (n == 0) return;
     const int64_t base = S->off[p];
-    const int o[3] = {(p % S->np[0]) * S->P[0], ((p / S->np[0]) % S->np[1]) * S->P[1],
-                      (p / (S->np[0] * S->np[1])) * S->P[2]};
+    const int P0 = S->P[0], P1 = S->P[1], P2 = ND == 3 ? S->P[2] : 0;
+    const int o[3] = {(p % S->np[0]) * P0, ((p / S->np[0]) % S->np[1]) * P1,
+                      ND == 3 ? (p / (S->np[0] * S->np[1])) * P2 : 0};
+    const int w0 = P0 + 3, w01 = w0 * (P1 + 3), total = w01 * (ND == 3 ? P2 + 3 : 1);
+    for (int t = tid; t < total; t += 256) tile[t] = 0.0;
+    __syncthreads();
     constexpr int PW = ND == 3 ? 4 : 2;
     const gptr_t<const T> X = glb((const T *)S->pos) + PW * base;
     const gptr_t<const T> M = glb((const T *)S->mom) + 4 * base;
     const double q = (double)S->q;
-    const int64_t fn0 = S->fn[0], fn1 = S->fn[1];
-    for (int k = threadIdx.x; k < n; k += blockDim.x) {
+    for (int k = tid; k < n; k += 256) {
         const double xs[3] = {(double)X[PW * k], (double)X[PW * k + 1], ND == 3 ? (double)X[PW * k + 2] : 0.0};
         const double qw = q * (double)M[4 * k + 3];
-        int i0[3];
+        const int P[3] = {P0, P1, P2};
+        int i0[3] = {0, 0, 0};
         double w[3][3];
+#pragma unroll
         for (int a = 0; a < ND; ++a) {
             i0[a] = (int)floor(xs[a] + 0.5);
             sweights(xs[a] - i0[a], w[a]);
+            i0[a] = min(max(i0[a], 0), P[a]);  // (a stored position lies in [0, P))
         }
-        const int nc = ND == 3 ? 3 : 1;
-        for (int c = 0; c < nc; ++c) {
-            const int gk = ND == 3 ? axis_node(o[2] + i0[2] + c - 1, S->n[2], S->periodic[2], 0) : 0;
+        const int r = i0[0] + w0 * i0[1] + (ND == 3 ? w01 * i0[2] : 0);  // tile entry of node i0 - 1
+#pragma unroll
+        for (int c = 0; c < (ND == 3 ? 3 : 1); ++c) {
             const double wz = ND == 3 ? w[2][c] : 1.0;
-            for (int b = 0; b < 3; ++b) {
-                const int gj = axis_node(o[1] + i0[1] + b - 1, S->n[1], S->periodic[1], 0);
-                for (int a = 0; a < 3; ++a) {
-                    const int gi = axis_node(o[0] + i0[0] + a - 1, S->n[0], S->periodic[0], 0);
-                    if (gi >= 0 && gj >= 0 && gk >= 0)
-                        atomicAdd(&out[gi + fn0 * (gj + fn1 * gk)], qw * w[0][a] * w[1][b] * wz);
-                }
-            }
+#pragma unroll
+            for (int b = 0; b < 3; ++b)
+#pragma unroll
+                for (int a = 0; a < 3; ++a)
+                    atomicAdd(&tile[r + a + w0 * b + w01 * c], qw * w[0][a] * w[1][b] * wz);
         }
+    }
+    __syncthreads();
+    const int64_t fn0 = S->fn[0], fn1 = S->fn[1];
+    for (int t = tid; t < total; t += 256) {
+        const double v = tile[t];
+        const int gi = axis_node(o[0] - 1 + t % w0, S->n[0], S->periodic[0], 0);
+        const int gj = axis_node(o[1] - 1 + (t / w0) % (P1 + 3), S->n[1], S->periodic[1], 0);
+        const int gk = ND == 3 ? axis_node(o[2] - 1 + t / w01, S->n[2], S->periodic[2], 0) : 0;
+        if (v != 0.0 && gi >= 0 && gj >= 0 && gk >= 0) atomicAdd(&out[gi + fn0 * (gj + fn1 * gk)], v);
     }
 }
 
@@ -179,13 +198,16 @@ void fill_doubles(double *p, int64_t n, double v, hipStream_t st)
 }
 
 template <typename T>
-void launch_rho(const SimDev<T> *sim, int npatch, int ndim, double *out, hipStream_t st)
+void launch_rho(const SimDev<T> *sim, int npatch, int ndim, const int P[3], double *out, hipStream_t st)
 {
     if (npatch <= 0) return;
+    // (at most 36 KB: 2-D patches have up to 64 x 64 cells, and 3-D ones also
+    // fit three larger 64-bit current tiles into LDS)
+    const size_t lds = sizeof(double) * (size_t)(P[0] + 3) * (P[1] + 3) * (ndim == 3 ? P[2] + 3 : 1);
     if (ndim == 3)
-        hipLaunchKernelGGL((k_rho<T, 3>), dim3(npatch), dim3(256), 0, st, sim, out);
+        hipLaunchKernelGGL((k_rho<T, 3>), dim3(npatch), dim3(256), lds, st, sim, out);
     else
-        hipLaunchKernelGGL((k_rho<T, 2>), dim3(npatch), dim3(256), 0, st, sim, out);
+        hipLaunchKernelGGL((k_rho<T, 2>), dim3(npatch), dim3(256), lds, st, sim, out);
 }
 
 template <typename T>
@@ -207,7 +229,7 @@ void launch_residuals(const SimDev<T> *sim, int ndim, int64_t fsize, int fpar, i
 int residual_partials() { return 4 * kResMaxBlocks; }
 
 #define PIC_INST(T)                                                                                \
-    template void launch_rho<T>(const SimDev<T> *, int, int, double *, hipStream_t);              \
+    template void launch_rho<T>(const SimDev<T> *, int, int, const int *, double *, hipStream_t); \
     template void launch_residuals<T>(const SimDev<T> *, int, int64_t, int, int, const double *,  \
                                       const double *, const double *, double *, double *,         \
                                       hipStream_t);

@@ -207,7 +207,7 @@ void launch_jfix(const SimDev<T> *sims, const int *list, const int64_t *prefix, 
 // that entry is then 0); `partials` holds residual_partials() doubles.
 void fill_doubles(double *p, int64_t n, double v, hipStream_t st);
 template <typename T>
-void launch_rho(const SimDev<T> *sim, int npatch, int ndim, double *out, hipStream_t st);
+void launch_rho(const SimDev<T> *sim, int npatch, int ndim, const int P[3], double *out, hipStream_t st);
 template <typename T>
 void launch_residuals(const SimDev<T> *sim, int ndim, int64_t fsize, int fpar, int jpar,
                       const double *rho, const double *rho0, const double *rho_prev,

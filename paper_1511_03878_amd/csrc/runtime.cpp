@@ -690,7 +690,7 @@ void SimImpl<T>::record_rho0()
 {
     if (!rho0_d) rho0_d = (double *)alloc.get(sizeof(double) * fsize);
     fill_doubles(rho0_d, fsize, 0.0, stream);
-    launch_rho<T>(view_d, npatch, nd, rho0_d, stream);
+    launch_rho<T>(view_d, npatch, nd, P, rho0_d, stream);
     hipcheck(hipGetLastError(), "rho launch");
     hipcheck(hipStreamSynchronize(stream), "sync");
     rho0_valid = true;
@@ -711,7 +711,7 @@ void SimImpl<T>::rho_noalloc(double *h, size_t count)
                                     " the allocation-free scratch holds");
     double *scr = noalloc_scratch();
     fill_doubles(scr, fsize, 0.0, stream);
-    launch_rho<T>(view_d, npatch, nd, scr, stream);
+    launch_rho<T>(view_d, npatch, nd, P, scr, stream);
     hipcheck(hipGetLastError(), "rho launch");
     hipcheck(hipMemcpyAsync(h, scr, sizeof(double) * fsize, hipMemcpyDeviceToHost, stream), "rho");
     hipcheck(hipStreamSynchronize(stream), "sync");
@@ -814,7 +814,7 @@ void SimImpl<T>::residuals(PicResiduals *out)
         throw;
     }
     fill_doubles(rho, fsize, 0.0, stream);
-    launch_rho<T>(view_d, npatch, nd, rho, stream);
+    launch_rho<T>(view_d, npatch, nd, P, rho, stream);
     const bool cont = rhoprev_d && rhoprev_step == s.step - 1;
     launch_residuals<T>(view_d, nd, fsize, (int)(s.step & 1), (int)((s.step + 1) & 1), rho,
                         rho0_valid ? rho0_d : nullptr, cont ? rhoprev_d : nullptr, part,
@@ -988,7 +988,7 @@ void SimImpl<T>::get_field(int comp, double *h)
     if (comp == PIC_RHO) {
         double *tmp = (double *)alloc.get(sizeof(double) * fsize);
         fill_doubles(tmp, fsize, 0.0, stream);
-        launch_rho<T>(view_d, npatch, nd, tmp, stream);
+        launch_rho<T>(view_d, npatch, nd, P, tmp, stream);
         hipcheck(hipGetLastError(), "rho launch");
         hipcheck(hipMemcpyAsync(h, tmp, sizeof(double) * fsize, hipMemcpyDeviceToHost, stream), "rho");
         hipcheck(hipStreamSynchronize(stream), "sync");
