@@ -178,6 +178,42 @@ __global__ void k_residual_final(const double *__restrict__ partials, int nblock
                                                  fmax(red[threadIdx.x][2], red[threadIdx.x][3]));
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void k_field_out(const SimDev<T> *__restrict__ S, int comp, int64_t nodes,
+                                                   double *__restrict__ out)
+{
+    const int64_t step = glb(S->st)->step;
+    const gptr_t<const T> f = glb((const T *)(comp < 6 ? S->F[step & 1][comp] : S->J[(step + 1) & 1][comp - 6]));
+    for (int64_t t = blockIdx.x * (int64_t)256 + threadIdx.x; t < nodes; t += (int64_t)gridDim.x * 256)
+        out[t] = (double)f[t];
+}
+
+// One workgroup per patch of the range (see launch_pack).
+template <typename T>
+__global__ __launch_bounds__(256) void k_pack(const SimDev<T> *__restrict__ S, int p0,
+                                              const int64_t *__restrict__ start, int64_t first, int64_t count,
+                                              PackOut out)
+{
+    const int p = p0 + blockIdx.x;
+    const int64_t a = start[p], base = S->off[p];
+    const int64_t lo = first > a ? first - a : 0, hi = min(start[p + 1] - a, first + count - a);
+    const double org[3] = {(double)((p % S->np[0]) * S->P[0]), (double)(((p / S->np[0]) % S->np[1]) * S->P[1]),
+                           (double)((p / (S->np[0] * S->np[1])) * S->P[2])};
+    const int pw = S->pw;
+    for (int64_t k = lo + threadIdx.x; k < hi; k += 256) {
+        const gptr_t<const T> x = glb((const T *)S->pos) + pw * (base + k);
+        const gptr_t<const T> m = glb((const T *)S->mom) + 4 * (base + k);
+        const int64_t t = a + k - first;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            if (out.v[c] && (c < 2 || pw == 4)) out.v[c][t] = org[c] + (double)x[c];
+            if (out.v[3 + c]) out.v[3 + c][t] = (double)m[c];
+        }
+        if (out.v[6]) out.v[6][t] = (double)m[3];
+        if (out.id) out.id[t] = pw == 4 ? pad_id<T>(x[3]) : glb((const int64_t *)S->id)[base + k];
+    }
+}
+
 __global__ void k_copy_int(const int *__restrict__ src, int *__restrict__ dst)
 {
     if (threadIdx.x == 0) *dst = *src;
@@ -228,7 +264,24 @@ void launch_residuals(const SimDev<T> *sim, int ndim, int64_t fsize, int fpar, i
 
 int residual_partials() { return 4 * kResMaxBlocks; }
 
+template <typename T>
+void launch_pack(const SimDev<T> *sim, int p0, int p1, const int64_t *start, int64_t first, int64_t count,
+                 const PackOut &out, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_pack<T>), dim3(p1 - p0 + 1), dim3(256), 0, st, sim, p0, start, first, count, out);
+}
+
+template <typename T>
+void launch_field_out(const SimDev<T> *sim, int comp, int64_t nodes, double *out, hipStream_t st)
+{
+    const int grid = (int)std::min<int64_t>((nodes + 255) / 256, 1024);
+    hipLaunchKernelGGL((k_field_out<T>), dim3(grid), dim3(256), 0, st, sim, comp, nodes, out);
+}
+
 #define PIC_INST(T)                                                                                \
+    template void launch_field_out<T>(const SimDev<T> *, int, int64_t, double *, hipStream_t);    \
+    template void launch_pack<T>(const SimDev<T> *, int, int, const int64_t *, int64_t, int64_t,  \
+                                 const PackOut &, hipStream_t);                                    \
     template void launch_rho<T>(const SimDev<T> *, int, int, const int *, double *, hipStream_t); \
     template void launch_residuals<T>(const SimDev<T> *, int, int64_t, int, int, const double *,  \
                                       const double *, const double *, double *, double *,         \

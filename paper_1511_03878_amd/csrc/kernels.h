@@ -213,6 +213,23 @@ void launch_residuals(const SimDev<T> *sim, int ndim, int64_t fsize, int fpar, i
                       const double *rho, const double *rho0, const double *rho_prev,
                       double *partials, double *out, hipStream_t st);
 int residual_partials();
+// Particles of the packed positions [first, first + count) in canonical
+// (patch, slot) order, component by component, into host-mapped memory:
+// `start` (host-mapped, npatch + 1 entries) holds the packed position of every
+// patch's first particle, and patches p0 .. p1 hold the range.  out: pointers
+// for x, y, z (global cell units), u_x, u_y, u_z, w (doubles) and the id
+// (64-bit integers), null where not wanted, each of `count` entries.
+struct PackOut {
+    double *v[7];
+    int64_t *id;
+};
+template <typename T>
+void launch_pack(const SimDev<T> *sim, int p0, int p1, const int64_t *start, int64_t first, int64_t count,
+                 const PackOut &out, hipStream_t st);
+// Field component comp (0..5: E, B of the current level; 6..8: the last
+// deposit) as doubles into host-mapped memory.
+template <typename T>
+void launch_field_out(const SimDev<T> *sim, int comp, int64_t nodes, double *out, hipStream_t st);
 // copy *src to *dst on the stream (one thread)
 void launch_copy_int(const int *src, int *dst, hipStream_t st);
 

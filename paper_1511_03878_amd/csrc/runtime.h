@@ -42,6 +42,23 @@ struct Allocator {
     void put(void *p);
 };
 
+// Pinned host memory for reading device data back.  Allocating it takes about
+// as long as reading a small simulation, so up to kPinnedKept blocks of at
+// most kPinnedMost bytes are kept for the next call of any handle (one call
+// owns a block until it returns it) and freed with the last handle.
+struct PinnedBlock {
+    char *buf = nullptr;
+    size_t bytes = 0;
+    explicit PinnedBlock(size_t need);  // buf is null when there is no pinned memory
+    ~PinnedBlock();
+    PinnedBlock(const PinnedBlock &) = delete;
+    PinnedBlock &operator=(const PinnedBlock &) = delete;
+};
+constexpr int kPinnedKept = 2;
+constexpr size_t kPinnedSmall = size_t(1) << 20;  // least block asked for
+constexpr size_t kPinnedMost = size_t(32) << 20;
+void pinned_handles(int change);  // a handle was made (1) or destroyed (-1)
+
 struct Timing {
     static constexpr int kKinds = 4;
     static const char *const names[kKinds];
@@ -124,6 +141,8 @@ struct SimImpl : SimBase {
     int *prefix_d = nullptr, *tprefix_d = nullptr;
     int32_t *nbt_d = nullptr;
     double *upart = nullptr, *kpart = nullptr;
+    std::vector<hipEvent_t> read_events;  // made on first use
+    bool reading_events(int n);
     int64_t max_tiles = 0;
     // diagnostics: the particles' charge density at load (the immobile ions
     // carry its negative) and at the last residual call
@@ -192,6 +211,9 @@ struct SimImpl : SimBase {
     void set_field(int comp, const double *h) override;
     void set_step(int64_t step) override;
     void get_field(int comp, double *h) override;
+    void copy_down(void *h, const void *src, size_t bytes);
+    template <typename S>
+    bool read_back(const S *src, int64_t cnt, double *h);
     SimState read_state() override;
     std::vector<int32_t> read_counts() override;
     int64_t num_particles() override;
@@ -272,7 +294,8 @@ struct BatchImpl : BatchBase {
     void launch_close_queue_pass();
     void launch_one_step();
     Timing &timing();
-    int run(int64_t max_steps, bool until_done);
+    std::vector<SimState> read_states();
+    int run(int64_t max_steps, bool until_done, const SimState *known = nullptr);
     void finished(std::vector<SimBase *> &out);
 };
 

@@ -1,0 +1,172 @@
+"""Choices of the step and of the read-back that depend on sizes, at the sizes
+where they change: shared launches against separate ones, work items of other
+sizes, the depth of 3-D field-update blocks, the lanes of the re-binning check,
+and read-backs that end inside a slot or a patch."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from tests import fixtures as W
+from tests.brute import rho_2d, rho_3d
+from tests.helpers import compare_fields, gpu_sim, neighbour_patch, neighbour_patch3
+
+pytestmark = pytest.mark.gpu
+
+FIELDS = ("Ex", "Ey", "Ez", "Bx", "By", "Bz", "Jx", "Jy", "Jz")
+S6 = 75.0 / 64.0 + 25.0 / 384.0 + 3.0 / 640.0
+
+
+def _announce(msg):
+    print(f"[gpu-test] {msg}", flush=True)
+
+
+def _box(case):
+    if case == "2d_open":
+        return W.lwfa_2d_small(n=(256, 64), patch=(16, 16), nsteps=12), {}
+    if case == "2d_sixth":
+        return W.uniform_2d(n=(72, 40), patch=(12, 8), ppc=6, T_keV=20.0, cfl=0.9 / S6), {"maxwell_order": 6}
+    if case == "3d":
+        return W.blob_3d(n=(24, 16, 20), patch=(8, 8, 4), T_keV=20.0, ppc0=3), {}
+    return W.blob_3d(n=(16, 12, 20), patch=(4, 4, 4), T_keV=20.0, ppc0=3, cfl=0.9 / S6), {"maxwell_order": 6}
+
+
+@pytest.mark.parametrize("case", ["2d_open", "2d_sixth", "3d", "3d_sixth"])
+def test_shared_launches_give_the_bits_of_separate_ones(case):
+    # timing every kernel group takes the separate launches on two streams
+    _announce(f"field update and re-binning in shared launches: {case}")
+    wl, kw = _box(case)
+    runs = []
+    for timed in (False, True):
+        g = gpu_sim(wl, 32, deterministic=1, **kw)
+        g.timing_enable(timed)
+        g.step(12)
+        runs.append([g.field(c) for c in FIELDS] + [g.history(0, 12)[0], g.counts(), *g.particles()[0], g.perm()])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("case", ["2d_sixth", "3d"])
+@pytest.mark.parametrize("chunk", [64, 1000])
+def test_item_size_does_not_change_the_state(case, chunk):
+    # (64: more items than workgroups, so most are claimed from the counter)
+    _announce(f"items of {chunk} particles against the default: {case}")
+    wl = (W.uniform_2d(n=(192, 160), patch=(32, 32), ppc=16, T_keV=20.0, cfl=0.9 / S6) if case == "2d_sixth"
+          else W.blob_3d(n=(32, 24, 16), patch=(8, 8, 8), T_keV=20.0, ppc0=6))
+    kw = {"maxwell_order": 6} if case == "2d_sixth" else {}
+    runs = []
+    for c in (0, chunk):
+        g = gpu_sim(wl, 32, deterministic=1, chunk=c, **kw)
+        g.step(8)
+        runs.append([g.field(f) for f in FIELDS] + [g.counts(), *g.particles()[0], g.perm()])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("n", [(40, 12, 18), (256, 128, 36)])
+def test_shallow_field_blocks_match_oracle(n):
+    # 4 and 8 planes per block; the last block of the z axis is partial
+    _announce(f"3-D vacuum fields {n} fp64")
+    d = (0.1, 0.13, 0.11)
+    grid = dict(ndim=3, n=list(n), d=list(d), dt=W.cfl_dt(d), patch=[4, 4, 2 if n[2] % 4 else 4],
+                periodic=[1, 1, 1], q=-1.0, m=1.0)
+    from paper_1511_03878_amd.sim import Sim
+    g = Sim(grid, 64)
+    g.set_particles([np.zeros(0)] * 3, [np.zeros(0)] * 3, np.zeros(0))
+    o = oracle.Sim(grid)
+    rng = np.random.default_rng(5)
+    for c in FIELDS[:6]:
+        f = rng.standard_normal(n[::-1])
+        g.set_field(c, f)
+        o.set_field(c, f)
+    steps = 8 if n[0] < 100 else 2
+    g.step(steps)
+    o.step(steps)
+    e, b = compare_fields(g, o)
+    assert e < 1e-12 and b < 1e-12, (e, b)
+    U, Uo = g.history(steps - 1, 1)[0][0], o.energy()[0]
+    assert abs(U - Uo) <= 1e-12 * abs(Uo)
+
+
+@pytest.mark.parametrize("nd", [2, 3])
+@pytest.mark.parametrize("moving", [0.001, 0.35, 1.0])
+def test_rebin_check_searches_any_number_of_vacated_slots(nd, moving):
+    # a few, thousands and all of a patch's particles leave
+    _announce(f"re-binning check: {nd}-D, {moving} of the particles leave")
+    wl = (W.uniform_2d(n=(128, 128), patch=(64, 64), ppc=2) if nd == 2
+          else W.blob_3d(n=(16, 16, 16), patch=(8, 8, 8), ppc0=8))
+    from paper_1511_03878_amd.sim import Sim
+    g = Sim(wl["grid"], 64)
+    g.set_particles(wl["x"], wl["u"], wl["w"])
+    counts, ids = g.counts(), g.perm()
+    rng = np.random.default_rng(9)
+    ndir = 9 if nd == 2 else 27
+    go = rng.random(ids.size) < moving
+    codes = np.full(ids.size, ndir // 2, dtype=np.uint8)
+    codes[go] = rng.integers(0, ndir, int(go.sum()))
+    codes[rng.random(ids.size) > 0.99] = 255
+    np_ = [wl["grid"]["n"][a] // wl["grid"]["patch"][a] for a in range(nd)]
+    owner = np.repeat(np.arange(counts.size), counts)
+    to = (lambda p, c: neighbour_patch(p, c, np_, (1, 1))) if nd == 2 else (lambda p, c: neighbour_patch3(p, c, np_))
+    dest = np.array([-1 if c == 255 else to(p, int(c)) for p, c in zip(owner, codes)], dtype=np.int32)
+    newcount, src = oracle.rebin(counts, dest)
+    g.rebin_codes(codes)
+    assert np.array_equal(g.counts(), newcount)
+    assert np.array_equal(g.perm(), ids[src])
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("n,patch", [((52, 20), (4, 20)), ((1000, 524), (50, 4)), ((1000, 525), (50, 25))])
+def test_fields_read_back_whole(n, patch, precision):
+    # below and above the size from which a grid is read in parts (2^19 nodes)
+    _announce(f"field read-back {n} fp{precision}")
+    from paper_1511_03878_amd.sim import Sim
+    d = (0.1, 0.1)
+    g = Sim(dict(ndim=2, n=list(n), d=list(d), dt=W.cfl_dt(d), patch=list(patch), periodic=[1, 1]), precision)
+    rng = np.random.default_rng(3)
+    for c in ("Ex", "Bz"):
+        f = rng.standard_normal(n[::-1]).astype(np.float32).astype(np.float64)
+        g.set_field(c, f)
+        assert np.array_equal(g.field(c), f)
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("nd,count", [(2, 0), (2, 1), (2, 65536), (2, 65537), (3, 3000), (3, 131075)])
+def test_particles_read_back_whole(nd, count, precision):
+    # runs of 2^16 particles: none, one, one exactly, and rests of 1 and 3
+    _announce(f"particle read-back {nd}-D {count} fp{precision}")
+    from paper_1511_03878_amd.sim import Sim
+    n, patch = ([48, 40], [8, 20]) if nd == 2 else ([16, 8, 24], [8, 4, 6])
+    d = [0.1] * nd
+    g = Sim(dict(ndim=nd, n=n, d=d, dt=W.cfl_dt(d), patch=patch, periodic=[1] * nd), precision)
+    rng = np.random.default_rng(count + nd)
+    # multiples of 2^-12: exact in FP32 as offsets in a patch and in the grid
+    x = [np.floor(rng.random(count) * n[a] * 4096) / 4096 for a in range(nd)]
+    x[0] = np.where(rng.random(count) < 0.3, x[0] % patch[0], x[0])  # uneven patches, some may be empty
+    u = [rng.standard_normal(count).astype(np.float32).astype(np.float64) for _ in range(3)]
+    w = rng.random(count).astype(np.float32).astype(np.float64)
+    g.set_particles(x, u, w)
+    gx, gu, gw, ids = g.particles()
+    assert np.array_equal(np.sort(ids), np.arange(count)) and np.array_equal(ids, g.perm())
+    pid = sum(np.floor(x[a]).astype(int) // patch[a] * int(np.prod([n[b] // patch[b] for b in range(a)]))
+              for a in range(nd))
+    assert np.array_equal(ids, np.argsort(pid, kind="stable"))
+    for got, ref in zip([*gx, *gu, gw], [*x, *u, w]):
+        assert np.array_equal(got, ref[ids])
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("n,patch", [((64, 64), (64, 64)), ((60, 35), (20, 7)), ((12, 10, 14), (6, 5, 7)),
+                                     ((8, 8, 4), (4, 8, 1))])
+def test_charge_density_of_any_patch_shape(n, patch, precision):
+    _announce(f"rho {n} patches {patch} fp{precision}")
+    wl = (W.uniform_2d(n=n, patch=patch, ppc=5, T_keV=20.0) if len(n) == 2
+          else W.blob_3d(n=n, patch=patch, ppc0=3, T_keV=20.0, blob_radius=3.0))
+    g = gpu_sim(wl, precision)
+    if patch != (64, 64):  # (the particle kernel's tiles of such a patch do not fit into LDS)
+        g.step(2)
+    x, _, w, _ = g.particles()
+    ref = rho_2d(x[0], x[1], w, -1.0, n) if len(n) == 2 else rho_3d(x, w, -1.0, n)
+    got = g.field("rho")
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
