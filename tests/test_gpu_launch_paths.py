@@ -89,6 +89,40 @@ def test_shallow_field_blocks_match_oracle(n):
     assert abs(U - Uo) <= 1e-12 * abs(Uo)
 
 
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("share", [0.0, 0.0005, 0.2])
+def test_particles_at_rest_without_fields(share, precision):
+    # weightless particles make no field: at rest they are passed over, but a
+    # share of them moves (units with and without a moving particle, slots
+    # that hold the code of a particle which left)
+    _announce(f"particles at rest without fields, {share} of them moving, fp{precision}")
+    wl = W.uniform_2d(n=(64, 48), patch=(16, 16), ppc=12, T_keV=200.0, seed=4)
+    if precision == 32:
+        wl = W.to_float32_state(wl)
+    go = np.random.default_rng(8).random(wl["w"].size) < share
+    wl["w"] = np.zeros_like(wl["w"])
+    wl["u"] = [np.where(go, v, 0.0) for v in wl["u"]]
+    from paper_1511_03878_amd.sim import Sim
+    g = Sim(wl["grid"], precision, chunk=300)
+    g.set_particles(wl["x"], wl["u"], wl["w"])
+    o = oracle.Sim(wl["grid"])
+    o.set_particles(wl["x"], wl["u"], wl["w"])
+    for steps in (1, 1, 12):
+        g.step(steps)
+        o.step(steps)
+        if precision == 64:
+            assert np.array_equal(g.counts(), o.counts()) and np.array_equal(g.perm(), o.particles()[3])
+            for a, b in zip(g.particles()[0], o.particles()[0]):
+                assert np.abs(np.asarray(a) - np.asarray(b)).max() < 1e-11
+    gx, gu, _, ids = g.particles()
+    back = np.argsort(ids)
+    for a in range(3):
+        assert np.array_equal(gu[a][back], np.asarray(wl["u"][a]))  # no field changes a momentum
+    for a in range(2):
+        assert np.array_equal(gx[a][back][~go], np.asarray(wl["x"][a])[~go])
+    assert not any(np.any(g.field(c)) for c in FIELDS)
+
+
 @pytest.mark.parametrize("nd", [2, 3])
 @pytest.mark.parametrize("moving", [0.001, 0.35, 1.0])
 def test_rebin_check_searches_any_number_of_vacated_slots(nd, moving):
