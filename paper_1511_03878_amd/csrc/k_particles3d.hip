@@ -75,7 +75,7 @@ __device__ __forceinline__ void deposit_window(long long *Jxt, long long *Jyt, l
 {
     W Ax[4], Bx[4], Ay[4], By[4];
 #pragma unroll
-    for (int k2 = 0; k2 < 4; ++k2) {
+    for (int k2 = 0; k2 < (FULL ? 4 : 3); ++k2) {
         Ax[k2] = S0x[k2] + W(0.5) * DSx[k2];
         Bx[k2] = W(0.5) * S0x[k2] + DSx[k2] * W(1.0 / 3.0);
         Ay[k2] = S0y[k2] + W(0.5) * DSy[k2];
@@ -86,7 +86,7 @@ __device__ __forceinline__ void deposit_window(long long *Jxt, long long *Jyt, l
     py[0] = dq * DSy[0];
     pz[0] = eq * DSz[0];
 #pragma unroll
-    for (int k2 = 1; k2 < 3; ++k2) {
+    for (int k2 = 1; k2 < (FULL ? 3 : 2); ++k2) {
         px[k2] = px[k2 - 1] + cq * DSx[k2];
         py[k2] = py[k2 - 1] + dq * DSy[k2];
         pz[k2] = pz[k2 - 1] + eq * DSz[k2];
@@ -95,7 +95,7 @@ __device__ __forceinline__ void deposit_window(long long *Jxt, long long *Jyt, l
     // then comes from one fused multiply-add)
     double pxd[3], pyd[3], pzd[3];
 #pragma unroll
-    for (int k2 = 0; k2 < 3; ++k2) {
+    for (int k2 = 0; k2 < (FULL ? 3 : 2); ++k2) {
         pxd[k2] = (double)px[k2] * fs;
         pyd[k2] = (double)py[k2] * fs;
         pzd[k2] = (double)pz[k2] * fs;
@@ -108,14 +108,14 @@ __device__ __forceinline__ void deposit_window(long long *Jxt, long long *Jyt, l
     const int mi = FULL && cx ? 4 : 3, mj = FULL && cy ? 4 : 3, mk = FULL && cz ? 4 : 3;
     // Jx: dual x (prefix index i), transverse (j, k)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = 0; kk < (FULL ? 4 : 3); ++kk) {
         if (kk >= mk) break;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < (FULL ? 4 : 3); ++j) {
             if (j >= mj) break;
             const W tr = Ay[j] * S0z[kk] + By[j] * DSz[kk];
 #pragma unroll
-            for (int i = 0; i < 3; ++i) {
+            for (int i = 0; i < (FULL ? 3 : 2); ++i) {
                 if (i >= ni) break;
                 fix_add_prod(&Jxt[rx + kk * jpl[0] + j * jrow[0] + i], pxd[i], (double)tr);
             }
@@ -123,14 +123,14 @@ __device__ __forceinline__ void deposit_window(long long *Jxt, long long *Jyt, l
     }
     // Jy: dual y (prefix index j), transverse (i, k)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = 0; kk < (FULL ? 4 : 3); ++kk) {
         if (kk >= mk) break;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < (FULL ? 4 : 3); ++i) {
             if (i >= mi) break;
             const W tr = Ax[i] * S0z[kk] + Bx[i] * DSz[kk];
 #pragma unroll
-            for (int j = 0; j < 3; ++j) {
+            for (int j = 0; j < (FULL ? 3 : 2); ++j) {
                 if (j >= nj) break;
                 fix_add_prod(&Jyt[ry + kk * jpl[1] + j * jrow[1] + i], pyd[j], (double)tr);
             }
@@ -138,14 +138,14 @@ __device__ __forceinline__ void deposit_window(long long *Jxt, long long *Jyt, l
     }
     // Jz: dual z (prefix index k), transverse (i, j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
+    for (int j = 0; j < (FULL ? 4 : 3); ++j) {
         if (j >= mj) break;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < (FULL ? 4 : 3); ++i) {
             if (i >= mi) break;
             const W tr = Ax[i] * S0y[j] + Bx[i] * DSy[j];
 #pragma unroll
-            for (int kk = 0; kk < 3; ++kk) {
+            for (int kk = 0; kk < (FULL ? 3 : 2); ++kk) {
                 if (kk >= nk) break;
                 fix_add_prod(&Jzt[rz + kk * jpl[2] + j * jrow[2] + i], pzd[kk], (double)tr);
             }
@@ -183,11 +183,11 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
 
     const int tid = threadIdx.x, ln = tid % kWave;
     const int total = *glb(nitems);
-    // items claimed one ahead, kinetic energy kept per wave (as in 2-D)
-    if (tid == 0) s_item[0] = atomicAdd(head, 1);
-    __syncthreads();
-    int idx = __builtin_amdgcn_readfirstlane(s_item[0]);
-    int slot = 1;
+    // first item by workgroup, further ones claimed one ahead, kinetic energy
+    // kept per wave (as in 2-D)
+    int idx = blockIdx.x;
+    int slot = 0;
+    bool first = true;
     double kin = 0.0;
     int kin_sim = -1, kin_p = 0;
     auto flush_kin = [&]() {
@@ -197,7 +197,7 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
     };
     while (idx < total) {
         int next = 0;
-        if (tid == 0) next = atomicAdd(head, 1);
+        if (tid == 0) next = (int)gridDim.x + atomicAdd(head, 1);
         const Item it = items[idx];
         const long long t_item = (stamps && tid == 0) ? wall_clock64() : 0;
         const int si = __builtin_amdgcn_readfirstlane(it.x & kItemSimMask);
@@ -301,7 +301,11 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                 }
             }
         }
-        for (int t = tid; t < jtot; t += BLOCK) Jt[t] = 0;
+        // (with one patch shape the flush leaves the current tile zero; with
+        // several, tiles of other items lay there)
+        if (PX == 0 || first)
+            for (int t = tid; t < jtot; t += BLOCK) Jt[t] = 0;
+        first = false;
         __syncthreads();
         if (tid == 0) s_item[slot] = next;  // read after the item's last barrier
 
@@ -434,10 +438,10 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                     // registers, so more waves fit); sums in the fixed-point tile
                     int mx, my, mz;
                     W S0x[4], DSx[4], S0y[4], DSy[4], S0z[4], DSz[4];
-                    const bool cx = window4(xl, (double)dxl, mx, S0x, DSx);
-                    const bool cy = window4(yl, (double)dyl, my, S0y, DSy);
-                    const bool cz = window4(zl, (double)dzl, mz, S0z, DSz);
-                    defer = cx || cy || cz;
+                    const bool sx0 = window3(xl, (double)dxl, mx, S0x, DSx);
+                    const bool sy0 = window3(yl, (double)dyl, my, S0y, DSy);
+                    const bool sz0 = window3(zl, (double)dzl, mz, S0z, DSz);
+                    defer = !(sx0 && sy0 && sz0);
                     if (!defer) {
                         const W qw = (W)wgt;
                         deposit_window<false>(Jxt, Jyt, Jzt, jpl, jrow, mx, my, mz, false, false, false, S0x,
@@ -513,9 +517,15 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                 const int gk = axis_node(oz - 2 + c, n2, 1, 0);
                 const int64_t k = gi + (int64_t)fn0 * (gj + (int64_t)fn1 * gk);
                 // entries outside a component's tile hold no current
-                const long long vx = a < jrow[0] ? Jt[jofs[0] + c * jpl[0] + b * jrow[0] + a] : 0;
-                const long long vy = b < jext(P1, 1, 1) ? Jt[jofs[1] + c * jpl[1] + b * jrow[1] + a] : 0;
-                const long long vz = c < jext(P2, 2, 2) ? Jt[jofs[2] + c * jpl[2] + b * jrow[2] + a] : 0;
+                long long vx = 0, vy = 0, vz = 0;
+                auto take = [&](long long *e) {
+                    const long long v = *e;
+                    if (PX) *e = 0;
+                    return v;
+                };
+                if (a < jrow[0]) vx = take(&Jt[jofs[0] + c * jpl[0] + b * jrow[0] + a]);
+                if (b < jext(P1, 1, 1)) vy = take(&Jt[jofs[1] + c * jpl[1] + b * jrow[1] + a]);
+                if (c < jext(P2, 2, 2)) vz = take(&Jt[jofs[2] + c * jpl[2] + b * jrow[2] + a]);
                 if (det) {
                     if (vx) gadd(glb(S.Jacc[0]) + k, (int64_t)vx);
                     if (vy) gadd(glb(S.Jacc[1]) + k, (int64_t)vy);
@@ -527,7 +537,9 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                 }
             }
         }
-        __syncthreads();
+        // (with one patch shape the next item writes only the field tile,
+        // which no wave reads any more, before its own first barrier)
+        if (PX == 0) __syncthreads();
         if (stamps && tid == 0) record_item(stamps + idx, t_item, si, p, it.w);
         idx = __builtin_amdgcn_readfirstlane(s_item[slot]);
         slot ^= 1;

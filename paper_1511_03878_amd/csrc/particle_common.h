@@ -66,6 +66,27 @@ __device__ __forceinline__ bool window4(T xl, double disp, int &m, W S0[4], W DS
     return sg != 0;
 }
 
+// The same on the three nodes of the old support, for a move after which the
+// nearest node is the same: returns false (S0, DS then hold nothing useful)
+// when it changed.  Same values as window4 gives such a move.
+template <typename T, typename W>
+__device__ __forceinline__ bool window3(T xl, double disp, int &m, W S0[3], W DS[3])
+{
+    const int i0 = (int)floor(xl + T(0.5));
+    const double d0 = (double)(xl - (T)i0);  // exact
+    const double d1 = d0 + disp;
+    m = i0 - 1;
+    double o0[3], o1[3];
+    qweights(d0, o0[0], o0[1], o0[2]);
+    qweights(d1, o1[0], o1[1], o1[2]);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        S0[k] = (W)o0[k];
+        DS[k] = (W)(o1[k] - o0[k]);
+    }
+    return d1 + 0.5 >= 0.0 && d1 + 0.5 < 1.0;  // (floor(d1 + 1/2) == 0)
+}
+
 // Reciprocal and reciprocal square root: hardware approximations (about one
 // ulp) for FP32, correctly rounded operations for FP64.
 __device__ __forceinline__ float rcp_(float x) { return __builtin_amdgcn_rcpf(x); }

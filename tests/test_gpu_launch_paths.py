@@ -64,6 +64,30 @@ def test_item_size_does_not_change_the_state(case, chunk):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("precision", [32, 64])
+def test_patch_shapes_mixed_in_a_3d_batch(precision):
+    # one kernel for all shapes of the batch; tiles of different sizes follow
+    # each other in a workgroup (small items: several per workgroup)
+    _announce(f"3-D batch of 8x8x8 and 4x4x8 patches fp{precision}")
+    from paper_1511_03878_amd.sim import Batch
+    wls = [W.blob_3d(n=(24, 16, 16), patch=(8, 8, 8), T_keV=20.0, ppc0=3),
+           W.blob_3d(n=(16, 24, 16), patch=(4, 4, 8), T_keV=20.0, ppc0=3, seed=6)]
+    runs = []
+    for together in (False, True):
+        sims = [gpu_sim(wl, precision, deterministic=1, chunk=64) for wl in wls]
+        if together:
+            b = Batch(precision, ndim=3)
+            for g in sims:
+                b.add(g, 6)
+            b.step(6)
+        else:
+            for g in sims:
+                g.step(6)
+        runs.append([v for g in sims for v in [*(g.field(f) for f in FIELDS), g.counts(), *g.particles()[0]]])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("n", [(40, 12, 18), (256, 128, 36)])
 def test_shallow_field_blocks_match_oracle(n):
     # 4 and 8 planes per block; the last block of the z axis is partial
