@@ -373,7 +373,9 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
 #pragma unroll
                     for (int k = 0; k < 4; ++k) {
                         ax_[k] = az * wx[k];
-                        bx_[k] = az * (0.5 * S0x[k] + DSx[k] * (1.0 / 3.0));
+                        // (which product the fma takes is stated: left open, workgroup
+                        // sizes differed in the last bit of Jz)
+                        bx_[k] = az * fma(DSx[k], 1.0 / 3.0, 0.5 * S0x[k]);
                     }
                     if (inplane) {
 #pragma unroll

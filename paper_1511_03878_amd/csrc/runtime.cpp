@@ -2059,8 +2059,21 @@ void BatchImpl<T>::build_tables()
     for (auto *m : members) use_graph = use_graph || m->desc.graph;
     // 512 threads (2-D FP64, 512 against 1024: 64 x 64 box 55 against 59 us
     // per step, 512 x 128 laser box 74 against 81, 4096 x 1024 laser box 688
-    // against 698)
-    block = 512;
+    // against 698), but 256 where that puts more workgroups on a CU and the
+    // items fill them: in FP64, whose registers allow two or three waves per
+    // SIMD, if two fit (512 / 256 threads, us per step: 1024 x 512 box in
+    // 16 x 16 patches 167 / 143, 96 x 64 x 64 box in 8 x 8 x 4 patches
+    // 443 / 412; 32 x 24 x 24 box, 170 items, 77 / 84), and for many short
+    // items (512 x 512 box in 8 x 8 patches, 4 per cell, FP32, 139 / 132,
+    // 64 x 64 x 64 box in 4 x 4 x 4 patches 304 / 282; 256 x 256 box, 1024
+    // items, 68 / 71).
+    const int64_t mean_patch = particles / std::max<int64_t>(occupied, 1);
+    const int64_t nitems = occupied * std::max<int64_t>(1, (mean_patch + chunk / 2) / chunk);
+    const int occ256 = nd == 3 ? particles3d_occupancy<T>(256, maxP0, maxP1, maxP2, patch_const)
+                               : particles_occupancy<T>(256, maxP0, maxP1);
+    const bool wide = sizeof(T) == 8 && nitems >= 2 * cu_count() && occ256 >= 2;
+    const bool short_items = nitems >= 8 * cu_count() && particles < 1024 * nitems && occ256 >= 3;
+    block = wide || short_items ? 256 : 512;
     for (auto *m : members) if (m->desc.block) block = m->desc.block;
     const int occ = std::max(1, nd == 3 ? particles3d_occupancy<T>(block, maxP0, maxP1, maxP2, patch_const)
                                         : particles_occupancy<T>(block, maxP0, maxP1));

@@ -64,6 +64,22 @@ def test_item_size_does_not_change_the_state(case, chunk):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("case", ["2d_fp64", "3d_fp64", "3d_fp32"])
+def test_workgroup_size_does_not_change_the_state(case):
+    # enough items that 256 threads are chosen, against 512
+    _announce(f"particle workgroups chosen against 512 threads: {case}")
+    wl = (W.uniform_2d(n=(256, 128), patch=(8, 8), ppc=4, T_keV=20.0) if case == "2d_fp64"
+          else W.blob_3d(n=(64, 32, 64) if case == "3d_fp32" else (32, 32, 32), patch=(4, 4, 4), T_keV=20.0,
+                         ppc0=2))
+    runs = []
+    for block in (0, 512):
+        g = gpu_sim(wl, 32 if case == "3d_fp32" else 64, deterministic=1, block=block)
+        g.step(6)
+        runs.append([g.field(f) for f in FIELDS] + [g.counts(), *g.particles()[0], g.perm()])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("precision", [32, 64])
 def test_patch_shapes_mixed_in_a_3d_batch(precision):
     # one kernel for all shapes of the batch; tiles of different sizes follow
