@@ -102,7 +102,7 @@ typedef struct {
     int32_t min_capacity;  /* 0 = the mean patch occupancy (at least 64) */
     int32_t chunk;         /* max particles per work item, at most 16384; 0 = chosen from the load */
     int32_t block;         /* threads per particle workgroup: 256, 512 or 1024; 0 = chosen, 256 or 512 */
-    int32_t field_tile;    /* Yee tile shape preset 0..5 (0 = default for the precision) */
+    int32_t field_tile;    /* 2-D Yee update: 0 = strips by marching waves, 1..5 = tile shape presets */
     int32_t lane_stride;   /* particles between adjacent lanes of the particle kernel, 1..64;
                               0 = 2 in 2-D, 4 in 3-D */
     int32_t graph;         /* 1: step in batches of 32 replayed from a captured HIP graph

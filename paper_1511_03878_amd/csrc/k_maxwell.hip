@@ -1,5 +1,5 @@
-// Field update of the 2-D patch-PIC step (the tile bodies are in maxwell2d.h):
-// the fused Yee kernel and the three passes of the sixth-order solver.
+// Field update of the 2-D patch-PIC step (the bodies are in maxwell2d.h):
+// the Yee kernels and the three passes of the sixth-order solver.
 #include "kernels.h"
 #include "maxwell2d.h"
 
@@ -14,6 +14,13 @@ __global__ __launch_bounds__(256) void k_maxwell2d(const SimDev<T> *__restrict__
     yee2d_tiles<T, TX, TY>(sims, nsims, tile_prefix, total, blockIdx.x, gridDim.x);
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void k_maxwell2d_march(const SimDev<T> *__restrict__ sims, int nsims,
+                                                         const int *__restrict__ tile_prefix, int total)
+{
+    yee2d_march<T>(sims, nsims, tile_prefix, total, blockIdx.x, gridDim.x);
+}
+
 template <typename T, int PASS>
 __global__ __launch_bounds__(256) void k_maxwell2d_hi(const SimDev<T> *__restrict__ sims, int nsims,
                                                       const int *__restrict__ tile_prefix, int total,
@@ -25,7 +32,7 @@ __global__ __launch_bounds__(256) void k_maxwell2d_hi(const SimDev<T> *__restric
 }  // namespace
 
 // Tile shapes (TX x TY nodes per workgroup) the tuner can choose from.
-// FP32 tiles hold 9 x (TX+3)(TY+3) floats of LDS, FP64 tiles doubles.
+// (0: the sixth-order solver only, Yee takes strips).  FP32 tiles hold 9 x (TX+3)(TY+3) floats of LDS, FP64 tiles doubles.
 namespace {
 constexpr int kTiles32[6][2] = {{64, 16}, {64, 8}, {128, 8}, {32, 16}, {32, 32}, {128, 4}};
 constexpr int kTiles64[6][2] = {{64, 8}, {32, 16}, {32, 8}, {16, 16}, {64, 4}, {128, 4}};
@@ -50,14 +57,16 @@ void launch_maxwell(const SimDev<T> *sims, int nsims, const int *tile_prefix, in
     const int p = (preset >= 0 && preset < 6) ? preset : 0;
     if (!yee) {
         // every simulation of the batch uses the sixth-order solver
+    } else if (p == 0) {
+        hipExtLaunchKernelGGL((k_maxwell2d_march<T>), dim3((total_tiles + kStripsPerWg - 1) / kStripsPerWg), dim3(256),
+                              0, st, ev.start, stop1, 0, sims, nsims, tile_prefix, total_tiles);
     } else if constexpr (sizeof(T) == 4) {
         switch (p) {
         case 1: PIC_MW(64, 8); break;
         case 2: PIC_MW(128, 8); break;
         case 3: PIC_MW(32, 16); break;
         case 4: PIC_MW(32, 32); break;
-        case 5: PIC_MW(128, 4); break;
-        default: PIC_MW(64, 16); break;
+        default: PIC_MW(128, 4); break;
         }
     } else {
         switch (p) {
@@ -65,8 +74,7 @@ void launch_maxwell(const SimDev<T> *sims, int nsims, const int *tile_prefix, in
         case 2: PIC_MW(32, 8); break;
         case 3: PIC_MW(16, 16); break;
         case 4: PIC_MW(64, 4); break;
-        case 5: PIC_MW(128, 4); break;
-        default: PIC_MW(64, 8); break;
+        default: PIC_MW(128, 4); break;
         }
     }
 #undef PIC_MW

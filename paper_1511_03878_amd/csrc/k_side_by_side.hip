@@ -1,5 +1,5 @@
 // Field update and re-binning side by side in one launch, for small batches:
-// the first workgroups take the field tiles, the others a pass of the
+// the first workgroups take the field strips or tiles, the others a pass of the
 // re-binning (the two share no data).  On two streams the fork and the join
 // cost about 7 and 6 us per step, as much as the passes of a small box
 // themselves (128 x 128 box: field update 10 us, re-binning 21 us); here they
@@ -20,7 +20,7 @@ constexpr int kNT = 256;
 static_assert(kMB == kNT && kYT == kNT && kRC == kNT, "one workgroup size for both parts");
 
 // PASS 0: Yee and count; 1, 2, 3: the sixth-order passes with count, check
-// and scatter.  The first field_wgs workgroups take the field tiles.
+// and scatter.  The first field_wgs workgroups take the fields.
 template <typename T, int ND, int PASS>
 __global__ __launch_bounds__(kNT) void k_fields_rebin(const SimDev<T> *__restrict__ sims, int nsims,
                                                       const int *__restrict__ tile_prefix, int tiles,
@@ -35,9 +35,8 @@ __global__ __launch_bounds__(kNT) void k_fields_rebin(const SimDev<T> *__restric
             if constexpr (PASS == 2) hi3d_e_tiles<T>(sims, nsims, tile_prefix, tiles, b, field_wgs);
             if constexpr (PASS == 3) hi3d_b_tiles<T, 2>(sims, nsims, tile_prefix, tiles, b, field_wgs);
         } else {
-            // (the default tile shape of the precision)
             if constexpr (PASS == 0)
-                yee2d_tiles<T, 64, sizeof(T) == 4 ? 16 : 8>(sims, nsims, tile_prefix, tiles, b, field_wgs);
+                yee2d_march<T>(sims, nsims, tile_prefix, tiles, b, field_wgs);
             else
                 hi2d_tiles<T, PASS - 1>(sims, nsims, tile_prefix, tiles, TX, TY, b, field_wgs);
         }
@@ -55,6 +54,7 @@ void launch_nd(const SimDev<T> *sims, int nsims, const int *tile_prefix, int til
 {
     int tx, ty;
     maxwell_tile<T>(0, tx, ty);
+    if (ND == kNDir2 && !hi_order) field_wgs = (tiles + kStripsPerWg - 1) / kStripsPerWg;
     const int check_wgs = (int)(((int64_t)patches * kCheckLanes<ND> + kNT - 1) / kNT);
 #define PIC_FR(PASS, N)                                                                                     \
     hipLaunchKernelGGL((k_fields_rebin<T, ND, PASS>), dim3(field_wgs + (N)), dim3(kNT), 0, st, sims, nsims, \

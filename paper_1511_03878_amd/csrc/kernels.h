@@ -158,11 +158,29 @@ void launch_merge(const SimDev<T> *sim, int npatch, int cmax, int iters, int for
 // other J buffer and accumulates the field energy of the incoming E, B.
 // yee: the batch holds simulations with the Yee solver; hi_order: it holds
 // simulations with the sixth-order solver, which take three further passes.
+// preset 0: the Yee simulations in strips (below) taken by marching
+// waves; 1..5: in tiles.  Sixth-order simulations always go by tiles.
 template <typename T>
 void launch_maxwell(const SimDev<T> *sims, int nsims, const int *tile_prefix, int total_tiles,
                     int grid, int preset, bool yee, bool hi_order, hipStream_t st, Ev2 ev = {});
 template <typename T>
 void maxwell_tile(int preset, int &tx, int &ty);
+
+// Strips of the 2-D Yee update: 61 nodes along x (the lanes of a wave without
+// its halo columns), 8 rows along y, or 4 on small grids, where the chain over
+// a strip's rows is what the launch takes (8 / 4 rows, us per step: 64 x 64
+// FP64 box 40.8 / 38.0, 460 x 180 60.1 / 58.8; 1536 x 384 laser box, 1248
+// strips, 94.2 / 97.5).
+constexpr int kStripCols = 61, kStripsPerWg = 4;
+inline int yee2d_rows(const int fn[3])
+{
+    return (int64_t)((fn[0] + kStripCols - 1) / kStripCols) * ((fn[1] + 7) / 8) >= 1024 ? 8 : 4;
+}
+inline int64_t yee2d_strips(const int fn[3])
+{
+    const int r = yee2d_rows(fn);
+    return (int64_t)((fn[0] + kStripCols - 1) / kStripCols) * ((fn[1] + r - 1) / r);
+}
 
 // Re-binning: count and stage leavers; check capacity; scatter (ndim 2 or 3:
 // 9 or 27 neighbour directions).
@@ -176,8 +194,8 @@ void launch_rebin_rest(const SimDev<T> *sims, int nsims, const int *patch_prefix
                        int ndim, hipStream_t st);
 
 // Field update and re-binning in shared launches (k_side_by_side.hip) on one
-// stream; every simulation of the batch uses the same solver and 2-D tiles
-// have the default shape.
+// stream; every simulation of the batch uses the same solver and the tile
+// preset is 0.
 template <typename T>
 void launch_fields_rebin(const SimDev<T> *sims, int nsims, const int *tile_prefix, int tiles, int field_wgs,
                          const int *patch_prefix, int patches, int rebin_grid, int ndim, bool hi_order,

@@ -1,8 +1,8 @@
-// Tile bodies of the 2-D field update: the fused Yee update and the passes of
-// the sixth-order solver.
+// Bodies of the 2-D field update: the fused Yee update (strips by marching
+// waves, or tiles) and the passes of the sixth-order solver.
 //
-// Yee: one workgroup updates a TX x TY tile of nodes with all three sweeps held in
-// LDS: B^{n+1/2} = B^n - dt/2 curl E^n, E^{n+1} = E^n + dt (curl B^{n+1/2} -
+// Yee: all three sweeps on a strip or a TX x TY tile of nodes, held in registers
+// or LDS: B^{n+1/2} = B^n - dt/2 curl E^n, E^{n+1} = E^n + dt (curl B^{n+1/2} -
 // J^{n+1/2}), B^{n+1} = B^{n+1/2} - dt/2 curl E^{n+1}.  B updates use forward
 // differences of E and E updates backward differences of B, so a one-node
 // halo on every side is enough for the three sweeps.  On an open x axis the
@@ -55,6 +55,51 @@ inline __device__ double beam_field(const double L[8], double t, double y)
 __device__ __forceinline__ int xcd_block(int b, int g)
 {
     return (g & 7) ? b : (b & 7) * (g >> 3) + (b >> 3);
+}
+
+// The updates with two products, and the Silver-Mueller ghosts, in one stated
+// fused form, so the tiles and the strips below give the same bits:
+// a p - b q, and the ghosts at x = 0 (E face values, B first inside) and x = L.
+template <typename T>
+__device__ __forceinline__ T curl2(T a, T p, T b, T q)
+{
+    return fma(a, p, -(b * q));
+}
+template <typename T>
+__device__ __forceinline__ T ghost_lo_bz(T ey, T b, T eyi, T r, T ir)
+{
+    return fma(-(T(1) - r), b, T(4) * eyi - T(2) * ey) * ir;
+}
+template <typename T>
+__device__ __forceinline__ T ghost_lo_by(T ez, T b, T ezi, T r, T ir)
+{
+    return fma(T(-4), ezi, fma(ez, T(2), -((T(1) - r) * b))) * ir;
+}
+template <typename T>
+__device__ __forceinline__ T ghost_hi(T e, T b, T r, T ir)  // e = Ey (Bz) or -Ez (By)
+{
+    return fma(e, T(2), -((T(1) - r) * b)) * ir;
+}
+
+// Incident Ey, Ez at the x = 0 face of step ls, row gj.
+template <typename T>
+__device__ __forceinline__ void incident_field(const SimDev<T> &S, int64_t ls, int gj, T &eyi, T &ezi)
+{
+    eyi = ezi = T(0);
+    if (ls < S.laser_steps) {
+        if (S.laser_ey) eyi = glb(S.laser_ey)[ls * S.n[1] + gj];
+        if (S.laser_ez) ezi = glb(S.laser_ez)[ls * S.n[1] + gj];
+    }
+    if (S.nlaser) {
+        const double t = ((double)ls + 0.5) * S.wdt;
+        double ey = 0.0, ez = 0.0;
+        for (int l = 0; l < S.nlaser; ++l) {
+            if (S.las_pol[l] == 1) ey += beam_field(S.las[l], t, ((double)gj + 0.5) * S.dd[1]);
+            else ez += beam_field(S.las[l], t, (double)gj * S.dd[1]);
+        }
+        eyi += (T)ey;
+        ezi += (T)ez;
+    }
 }
 
 // Yee tiles of workgroup b of g (256 threads).
@@ -163,7 +208,7 @@ __device__ __forceinline__ void yee2d_tiles(const SimDev<T> *__restrict__ sims, 
             const int c = b * W + a;
             sB[0][c] -= h * (sE[2][c + W] - sE[2][c]) * iy;
             sB[1][c] += h * (sE[2][c + 1] - sE[2][c]) * ix;
-            sB[2][c] -= h * ((sE[1][c + 1] - sE[1][c]) * ix - (sE[0][c + W] - sE[0][c]) * iy);
+            sB[2][c] -= h * curl2(sE[1][c + 1] - sE[1][c], ix, sE[0][c + W] - sE[0][c], iy);
         }
         __syncthreads();
 
@@ -172,35 +217,20 @@ __device__ __forceinline__ void yee2d_tiles(const SimDev<T> *__restrict__ sims, 
             const T r = dt * ix;
             const T ir = T(1) / (T(1) + r);
             if (X0 == 0) {
-                const int64_t ls = stepn;
                 for (int b = tid; b < H; b += 256) {
-                    const int gj = wrap_idx(Y0 - 1 + b, n1);
-                    T eyi = T(0), ezi = T(0);
-                    if (ls < S.laser_steps) {
-                        if (S.laser_ey) eyi = glb(S.laser_ey)[ls * n1 + gj];
-                        if (S.laser_ez) ezi = glb(S.laser_ez)[ls * n1 + gj];
-                    }
-                    if (S.nlaser) {
-                        const double t = ((double)ls + 0.5) * S.wdt;
-                        double ey = 0.0, ez = 0.0;
-                        for (int l = 0; l < S.nlaser; ++l) {
-                            if (S.las_pol[l] == 1) ey += beam_field(S.las[l], t, ((double)gj + 0.5) * S.dd[1]);
-                            else ez += beam_field(S.las[l], t, (double)gj * S.dd[1]);
-                        }
-                        eyi += (T)ey;
-                        ezi += (T)ez;
-                    }
+                    T eyi, ezi;
+                    incident_field(S, stepn, wrap_idx(Y0 - 1 + b, n1), eyi, ezi);
                     const int c = b * W;  // a = 0 is x-node -1 (dual -1/2 for By, Bz)
-                    sB[2][c] = (T(4) * eyi - T(2) * sE[1][c + 1] - (T(1) - r) * sB[2][c + 1]) * ir;
-                    sB[1][c] = (T(2) * sE[2][c + 1] - (T(1) - r) * sB[1][c + 1] - T(4) * ezi) * ir;
+                    sB[2][c] = ghost_lo_bz(sE[1][c + 1], sB[2][c + 1], eyi, r, ir);
+                    sB[1][c] = ghost_lo_by(sE[2][c + 1], sB[1][c + 1], ezi, r, ir);
                 }
             }
             const int ag = n0 - X0 + 1;  // local column of dual x index n0 (x = L + 1/2)
             if (ag >= 1 && ag <= TX + 1) {
                 for (int b = tid; b < H; b += 256) {
                     const int c = b * W + ag;
-                    sB[2][c] = (T(2) * sE[1][c] - (T(1) - r) * sB[2][c - 1]) * ir;
-                    sB[1][c] = (-T(2) * sE[2][c] - (T(1) - r) * sB[1][c - 1]) * ir;
+                    sB[2][c] = ghost_hi(sE[1][c], sB[2][c - 1], r, ir);
+                    sB[1][c] = ghost_hi(-sE[2][c], sB[1][c - 1], r, ir);
                 }
             }
             __syncthreads();
@@ -215,7 +245,7 @@ __device__ __forceinline__ void yee2d_tiles(const SimDev<T> *__restrict__ sims, 
             const int c = b * W + a;
             sE[0][c] += dt * ((sB[2][c] - sB[2][c - W]) * iy - jv[r][0]);
             sE[1][c] += dt * (-(sB[2][c] - sB[2][c - 1]) * ix - jv[r][1]);
-            sE[2][c] += dt * ((sB[1][c] - sB[1][c - 1]) * ix - (sB[0][c] - sB[0][c - W]) * iy - jv[r][2]);
+            sE[2][c] += dt * (curl2(sB[1][c] - sB[1][c - 1], ix, sB[0][c] - sB[0][c - W], iy) - jv[r][2]);
         }
         __syncthreads();
 
@@ -227,7 +257,7 @@ __device__ __forceinline__ void yee2d_tiles(const SimDev<T> *__restrict__ sims, 
             const int c = b * W + a;
             const T bx = sB[0][c] - h * (sE[2][c + W] - sE[2][c]) * iy;
             const T by = sB[1][c] + h * (sE[2][c + 1] - sE[2][c]) * ix;
-            const T bz = sB[2][c] - h * ((sE[1][c + 1] - sE[1][c]) * ix - (sE[0][c + W] - sE[0][c]) * iy);
+            const T bz = sB[2][c] - h * curl2(sE[1][c + 1] - sE[1][c], ix, sE[0][c + W] - sE[0][c], iy);
             // own nodes are inside the periodic range; on an open axis the dual
             // components stop one node short
             const bool dx_ok = per0 || gi <= n0 - 1;
@@ -253,6 +283,197 @@ __device__ __forceinline__ void yee2d_tiles(const SimDev<T> *__restrict__ sims, 
         if (tid == 0)
             glb(S.upart)[lt] = 0.5 * S.vcell * (s_red[0] + s_red[1] + s_red[2] + s_red[3]);
         __syncthreads();
+    }
+}
+
+// The same update by waves that march along y (the default; the tiles serve
+// the presets that the tuner tries).  A wave takes a strip of kStripCols x
+// S.yee_bz nodes, one column per lane (lane 0 the column before the strip, lanes
+// 62 and 63 the two after it), keeps the rows of the three sweeps in registers,
+// reads x neighbours from the neighbouring lane, and has the next four rows in
+// flight while it updates one; no LDS, no barrier.  The tiles load, update and
+// store in turn with two workgroups per CU (197 VGPRs), so latency bounds them;
+// this kernel runs at 4.1 TB/s from HBM (4096 x 1024 nodes; a copy of as many
+// arrays runs at 5.2 - 6.5) and 5.1 from the last-level cache.  us per launch,
+// tiles / strips, FP32: 4096 x 1024 99 / 73, 2048 x 1024 52 / 29, 1024 x 1024
+// 26 / 18; FP64: 163 / 141, 90 / 72, 38 / 32.  In the step: 4096 x 1024 laser
+// box 321 -> 288 us, 1536 x 384 102 -> 94.  Rows per strip: 16 take 80 us at
+// 4096 x 1024 (too few waves), 6 take 74; 56 columns, which makes rows of
+// stores start on 32 bytes, 75.  Rows are read and written through buffer
+// descriptors whose bounds check drops the lanes that have no node (and reads
+// zero for them), so no access sits behind a branch.
+constexpr int kMarchAhead = 4;
+
+// Descriptor of a row of n nodes; offsets in bytes, kNoNode is past every row.
+constexpr uint32_t kNoNode = 0x80000000u;
+template <typename T>
+struct RowBuf {
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ RowBuf(const T *row, int n)
+        : r(__builtin_amdgcn_make_buffer_rsrc((void *)row, 0, n * (int)sizeof(T), 0x00027000))
+    {
+    }
+    __device__ __forceinline__ T load(uint32_t off) const
+    {
+        if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+        else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    }
+    __device__ __forceinline__ void store(uint32_t off, T x) const
+    {
+        if constexpr (sizeof(T) == 4) {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), r, off, 0, 0);
+        } else {
+            typedef uint32_t W2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(W2, x), r, off, 0, 0);
+        }
+    }
+};
+
+// Strips of workgroup wg of nwg (256 threads, a strip per wave).
+template <typename T>
+__device__ __forceinline__ void yee2d_march(const SimDev<T> *__restrict__ sims, int nsims,
+                                            const int *__restrict__ tile_prefix, int total, int wg, int nwg)
+{
+    const int ln = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (int tile = kStripsPerWg * xcd_block(wg, nwg) + wv; tile < total; tile += kStripsPerWg * nwg) {
+        const int s = find_sim(tile_prefix, nsims, tile);
+        const SimDev<T> &S = sims[s];
+        if (!glb(S.st)->active || S.morder == 6) continue;
+        const int lt = tile - tile_prefix[s];
+        const int n0 = S.n[0], n1 = S.n[1], fn0 = S.fn[0];
+        const int per0 = S.periodic[0];  // (y is periodic in 2-D)
+        const int ntx = (fn0 + kStripCols - 1) / kStripCols;
+        const int X0 = (lt % ntx) * kStripCols, Y0 = (lt / ntx) * S.yee_bz;
+        const int rows = min(S.yee_bz, n1 - Y0);
+        const int64_t stepn = glb(S.st)->step;
+        T *const *Jc = S.J[stepn & 1];
+        T *const *Jn = S.J[(stepn + 1) & 1];
+        T *const *Fc = S.F[stepn & 1];
+        T *const *Fn = S.F[(stepn + 1) & 1];
+
+        // byte offsets of the lane's column in a row, for primal and dual x;
+        // columns more than one past the last stored node feed no update
+        const int gi = X0 - 1 + ln;
+        const int ip = gi <= fn0 + 1 ? axis_node(gi, n0, per0, 0) : -1;
+        const int id = gi <= fn0 + 1 ? axis_node(gi, n0, per0, 1) : -1;
+        const uint32_t op = ip >= 0 ? (uint32_t)ip * (uint32_t)sizeof(T) : kNoNode;
+        const uint32_t od = id >= 0 ? (uint32_t)id * (uint32_t)sizeof(T) : kNoNode;
+        const bool own = ln >= 1 && ln <= kStripCols && gi < fn0;
+        const uint32_t wp = own ? op : kNoNode, wd = own ? od : kNoNode;
+        // staggering: Ex (d,p) Ey (p,d) Ez (p,p) Bx (p,d) By (d,p) Bz (d,d)
+        struct Row {
+            T e[3], b[3], j[3];
+        };
+        // row b of the strip is row Y0 - 1 + b of the grid: E of rows 0 .. rows + 2,
+        // B up to rows + 1, J up to rows + 1 from 1 (others read as zero, from an
+        // empty descriptor)
+        auto load_row = [&](int b, Row &r) {
+            int gj = Y0 - 1 + min(b, rows + 2);
+            gj += gj < 0 ? n1 : 0;
+            gj -= gj >= n1 ? n1 : 0;
+            const int64_t ro = (int64_t)fn0 * gj;
+            const int ne = b <= rows + 2 ? fn0 : 0, nb = b <= rows + 1 ? fn0 : 0, nj = b >= 1 ? nb : 0;
+            r.e[0] = RowBuf<T>(Fc[0] + ro, ne).load(od);
+            r.e[1] = RowBuf<T>(Fc[1] + ro, ne).load(op);
+            r.e[2] = RowBuf<T>(Fc[2] + ro, ne).load(op);
+            r.b[0] = RowBuf<T>(Fc[3] + ro, nb).load(op);
+            r.b[1] = RowBuf<T>(Fc[4] + ro, nb).load(od);
+            r.b[2] = RowBuf<T>(Fc[5] + ro, nb).load(od);
+            r.j[0] = RowBuf<T>(Jc[0] + ro, nj).load(od);
+            r.j[1] = RowBuf<T>(Jc[1] + ro, nj).load(op);
+            r.j[2] = RowBuf<T>(Jc[2] + ro, nj).load(op);
+        };
+        const bool lo = !per0 && X0 == 0;
+        // incident field of row ln (evaluated first: it takes many registers)
+        T eyi = T(0), ezi = T(0);
+        if (lo && ln < rows + 2) incident_field(S, stepn, wrap_idx(Y0 - 1 + ln, n1), eyi, ezi);
+        Row r0, cur, nxt, ring[kMarchAhead];
+        load_row(0, r0);
+        load_row(1, cur);
+        load_row(2, nxt);
+#pragma unroll
+        for (int u = 0; u < kMarchAhead; ++u) load_row(3 + u, ring[u]);
+
+        const T dt = S.dt, h = T(0.5) * S.dt;
+        const T ix = T(1) / S.d[0], iy = T(1) / S.d[1];
+        const T sm = dt * ix, ism = T(1) / (T(1) + sm);
+        const int ag = per0 ? -1 : n0 - X0 + 1;  // lane of dual x index n0 (x = L + 1/2)
+        auto up = [&](T x) { return __shfl_down(x, 1); };  // value of the next column
+        auto dn = [&](T x) { return __shfl_up(x, 1); };    // ... of the previous one
+
+        // the three sweeps on a row; e, en: E of the row and of the next
+        double esum = 0.0;
+        auto b_half = [&](const T b[3], const T e[3], const T en[3], T o[3]) {
+            o[0] = b[0] - h * (en[2] - e[2]) * iy;
+            o[1] = b[1] + h * (up(e[2]) - e[2]) * ix;
+            o[2] = b[2] - h * curl2(up(e[1]) - e[1], ix, en[0] - e[0], iy);
+        };
+        // B^{n+1/2} of the row in c (row number b), with ghosts and field energy
+        auto sweep1 = [&](int b, const Row &c, const Row &n, T o[3]) {
+            b_half(c.b, c.e, n.e, o);
+            if (lo) {
+                const T ey = up(c.e[1]), ez = up(c.e[2]), bz = up(o[2]), by = up(o[1]);
+                const T iy_ = __shfl(eyi, b), iz_ = __shfl(ezi, b);
+                if (ln == 0) {
+                    o[2] = ghost_lo_bz(ey, bz, iy_, sm, ism);
+                    o[1] = ghost_lo_by(ez, by, iz_, sm, ism);
+                }
+            }
+            if (ag >= 1 && ag <= kStripCols + 1) {
+                const T bz = dn(o[2]), by = dn(o[1]);
+                if (ln == ag) {
+                    o[2] = ghost_hi(c.e[1], bz, sm, ism);
+                    o[1] = ghost_hi(-c.e[2], by, sm, ism);
+                }
+            }
+            double en = 0.0;
+#pragma unroll
+            for (int k = 0; k < 3; ++k) en += (double)c.e[k] * (double)c.e[k] + (double)c.b[k] * (double)c.b[k];
+            esum += own && b <= rows ? en : 0.0;
+        };
+        // E^{n+1} of the row in c from B^{n+1/2} of it (bh) and of the previous row
+        auto sweep2 = [&](const Row &c, const T bh[3], const T bp[3], T o[3]) {
+            o[0] = c.e[0] + dt * ((bh[2] - bp[2]) * iy - c.j[0]);
+            o[1] = c.e[1] + dt * (-(bh[2] - dn(bh[2])) * ix - c.j[1]);
+            o[2] = c.e[2] + dt * (curl2(bh[1] - dn(bh[1]), ix, bh[0] - bp[0], iy) - c.j[2]);
+        };
+
+        T bh[3], bp[3], ec[3];  // B^{n+1/2} and E^{n+1} of the row to write, B of the one before
+        b_half(r0.b, r0.e, cur.e, bp);
+        sweep1(1, cur, nxt, bh);
+        sweep2(cur, bh, bp, ec);
+        for (int b0 = 1; b0 <= rows; b0 += kMarchAhead) {
+#pragma unroll
+            for (int u = 0; u < kMarchAhead; ++u) {
+                const int b = b0 + u;  // row to write; nxt holds row b + 1, ring[u] row b + 2
+                if (b > rows) break;
+                T bn[3], en[3], o[3];
+                sweep1(b + 1, nxt, ring[u], bn);
+                sweep2(nxt, bn, bh, en);
+                b_half(bh, ec, en, o);
+                const int64_t ro = (int64_t)fn0 * (Y0 - 1 + b);
+                RowBuf<T>(Fn[0] + ro, fn0).store(wd, ec[0]);
+                RowBuf<T>(Fn[1] + ro, fn0).store(wp, ec[1]);
+                RowBuf<T>(Fn[2] + ro, fn0).store(wp, ec[2]);
+                RowBuf<T>(Fn[3] + ro, fn0).store(wp, o[0]);
+                RowBuf<T>(Fn[4] + ro, fn0).store(wd, o[1]);
+                RowBuf<T>(Fn[5] + ro, fn0).store(wd, o[2]);
+                RowBuf<T>(Jn[0] + ro, fn0).store(wd, T(0));
+                RowBuf<T>(Jn[1] + ro, fn0).store(wp, T(0));
+                RowBuf<T>(Jn[2] + ro, fn0).store(wp, T(0));
+                nxt = ring[u];
+                load_row(b + 2 + kMarchAhead, ring[u]);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    ec[k] = en[k];
+                    bh[k] = bn[k];
+                }
+            }
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) esum += __shfl_xor(esum, o, 64);
+        if (ln == 0) glb(S.upart)[lt] = 0.5 * S.vcell * esum;
     }
 }
 

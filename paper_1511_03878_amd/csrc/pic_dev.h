@@ -67,7 +67,7 @@ struct SimDev {
     int ndim;
     int lane_stride;   // particles between consecutive lanes of a wave
     int morder;        // field solver order: 2 (Yee) or 6
-    int yee_bz;        // node planes of a 3-D Yee block
+    int yee_bz;        // node planes of a 3-D Yee block, rows of a 2-D Yee strip
     // moving window (2-D, open x): jumps of P[0] cells, cold lattice injection
     int win;           // 1: the window moves
     int wppc[2];       // injected particles per cell along x, y

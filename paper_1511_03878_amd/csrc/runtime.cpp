@@ -539,7 +539,7 @@ void SimImpl<T>::refresh_view()
     V.ndim = nd;
     V.lane_stride = lane_stride;
     V.morder = desc.maxwell_order == 6 ? 6 : 2;
-    V.yee_bz = nd == 3 ? yee3_planes(fn) : 0;
+    V.yee_bz = nd == 3 ? yee3_planes(fn) : yee2d_rows(fn);
     V.win = win_on ? 1 : 0;
     V.wppc[0] = win_ppc[0];
     V.wppc[1] = win_ppc[1];
@@ -2000,9 +2000,11 @@ void BatchImpl<T>::build_tables()
     for (int i = 0; i < ns; ++i) {
         SimImpl<T> *m = members[i];
         pp[i + 1] = pp[i] + m->npatch;
-        // Yee tiles: TX x TY node tiles in 2-D, blocks of nodes in 3-D
+        // field-update tiles: strips or TX x TY node tiles in 2-D, blocks of nodes in 3-D
         const int ntiles = nd == 3 ? (int)maxwell3d_tiles(m->fn, m->desc.maxwell_order)
-                                   : ((m->fn[0] + tx - 1) / tx) * ((m->fn[1] + ty - 1) / ty);
+                           : tile_preset == 0 && m->desc.maxwell_order != 6
+                               ? (int)yee2d_strips(m->fn)
+                               : ((m->fn[0] + tx - 1) / tx) * ((m->fn[1] + ty - 1) / ty);
         tp[i + 1] = tp[i] + ntiles;
         const int own[2] = {0, ntiles};
         hipcheck(hipMemcpyAsync(m->tprefix_d, own, sizeof(own), hipMemcpyHostToDevice, stream), "tile count");

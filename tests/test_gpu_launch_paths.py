@@ -130,6 +130,35 @@ def test_shallow_field_blocks_match_oracle(n):
 
 
 @pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("periodic", [1, 0])
+@pytest.mark.parametrize("n", [(64, 8), (60, 12), (184, 42), (8, 5000), (976, 602)])
+def test_field_strips_give_the_bits_of_tiles(n, periodic, precision):
+    # strips of 61 columns and 4 or 8 rows (partial ones, a grid narrower than a
+    # strip, the x = L ghost in the first and last lanes) against 2-D tiles
+    _announce(f"2-D vacuum fields {n} periodic {periodic} fp{precision}: strips against tiles")
+    from paper_1511_03878_amd.sim import Sim
+    d = (0.1, 0.13)
+    grid = dict(ndim=2, n=list(n), d=list(d), dt=W.cfl_dt(d), patch=[4, 2], periodic=[periodic, 1], q=-1.0, m=1.0)
+    runs = []
+    for tile in (0, 1):
+        g = Sim(grid, precision, field_tile=tile)
+        g.set_particles([np.zeros(0)] * 2, [np.zeros(0)] * 3, np.zeros(0))
+        rng = np.random.default_rng(11)
+        for c in FIELDS[:6]:
+            g.set_field(c, rng.standard_normal(g.field(c).shape))
+        if not periodic:
+            t = np.arange(6)[:, None] + 0.1 * np.arange(n[1])[None]
+            g.set_laser(ey=np.sin(t), ez=np.cos(t))
+            g.add_laser(dict(a0=1.0, omega0=1.0, w0=5.0, tau=4.0, t0=1.0, x_focus=3.0, y_center=2.0, phase=0.2))
+        g.step(6)
+        runs.append(([g.field(c) for c in FIELDS[:6]], g.history(0, 6)[0]))
+    for a, b in zip(runs[0][0], runs[1][0]):
+        assert np.array_equal(a, b)
+    # the energies add the same squares in another order
+    assert np.abs(runs[0][1] - runs[1][1]).max() <= 1e-12 * np.abs(runs[1][1]).max()
+
+
+@pytest.mark.parametrize("precision", [32, 64])
 @pytest.mark.parametrize("share", [0.0, 0.0005, 0.2])
 def test_particles_at_rest_without_fields(share, precision):
     # weightless particles make no field: at rest they are passed over, but a
