@@ -75,6 +75,7 @@ struct QueueArgs {
     int max_items;
     int chunk;                // max particles per item
     int total_patches;        // patch_prefix[nsims]
+    int total_tiles;          // tile_prefix[nsims]
     // scratch of the grid-wide queue build (kQueueScratch ints): bucket
     // counts, bucket cursors, then one participation word per simulation
     int *scratch;

@@ -2177,6 +2177,7 @@ QueueArgs BatchImpl<T>::queue_args() const
     qa.max_items = table_cap_items;
     qa.chunk = chunk;
     qa.total_patches = total_patches;
+    qa.total_tiles = total_tiles;
     qa.scratch = qscratch_d;
     return qa;
 }
