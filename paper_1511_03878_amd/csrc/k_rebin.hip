@@ -33,9 +33,11 @@ namespace {
 // than 256 beside the field update, in 2-D and 3-D)
 constexpr int kRB = 128;
 
+// (held to 64 VGPRs, 8 waves per SIMD: with 84 the 512 x 512 box in 8 x 8
+// patches took 130 us per step, not 125)
 template <typename T, int ND, int NT>
-__global__ __launch_bounds__(NT) void k_rebin_count(const SimDev<T> *__restrict__ sims, int nsims,
-                                                    const int *__restrict__ patch_prefix, int total)
+__global__ __launch_bounds__(NT, 8) void k_rebin_count(const SimDev<T> *__restrict__ sims, int nsims,
+                                                       const int *__restrict__ patch_prefix, int total)
 {
     rebin_count_patches<T, ND, NT>(sims, nsims, patch_prefix, total, blockIdx.x, gridDim.x);
 }

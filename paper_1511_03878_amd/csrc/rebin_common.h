@@ -39,42 +39,35 @@ __device__ __forceinline__ void copy_particle(const SimDev<T> &S, int64_t from, 
 // Count pass.  Each wave of the workgroup owns a contiguous range of the
 // patch's slots and loads the destination codes of up to kU x 64 of them at
 // once (one batch; a patch of at most waves x kU x 64 particles is one batch).
-// Leaver counts per key come from ballots, one per key present in a 64-slot
-// chunk, and are kept lane-indexed in a register (lane k: key k, lane kKeys:
-// all keys).  After one exchange of the per-wave counts through LDS every wave
-// knows where its leavers go: the vacated slots are listed in slot order and
-// the staged leavers are queued in a per-wave LDS ring, which is drained 64
-// entries at a time (one lane per particle, so the particle loads of 64
-// leavers are in flight together).
+// It lists the batch's leavers in LDS in slot order (a ballot per 64 slots) and
+// counts them per key with LDS atomics.  After one exchange of the per-wave
+// counts every wave knows where its leavers go; it then takes its list 64
+// leavers at a time, one per lane: the vacated slots are a plain copy of the
+// list, the rank among the leavers of a key comes from one ballot per key
+// present, and the particle loads of the 64 are in flight together.  The chain
+// of these rounds bounds the pass (a ballot per key and 64 slots, twice, and the
+// codes of a second batch fetched again took, us per step: 64 x 48 x 40 box
+// 174 -> 156, 128 x 128 46 -> 43, 512 x 128 FP64 laser box 54 -> 48, 1024 x 1024
+// 436 -> 426, 256 x 128 x 128 2276 -> 2242).
 // threads of the count workgroup: 256 in 2-D (512 and 128 slower), and in 3-D
 // one wave per patch where the patches fill the chip (about a hundred
 // leavers per 8^3 patch; measured beside the field update, smaller workgroups
 // keep more patches in flight), else 256 (one wave's walk of a patch is then
-// the whole pass: 64 x 48 x 40 box, 240 patches, 85 against 29 us)
+// the whole pass: 64 x 48 x 40 box, 240 patches, 85 against 29 us,
+// measured before the list below)
 constexpr int kRC = 256;
 constexpr int kRC3 = 64;
 constexpr int kRC3Patches = 2048;
-constexpr int kU = 16;    // 64-slot chunks per batch of code loads (63 VGPRs: 8 waves per SIMD)
-constexpr int kRing = 128;
-
-template <typename T>
-__device__ __forceinline__ void drain_ring(const SimDev<T> &S, int64_t base, const int2 *ring,
-                                           int &head, int tail, int lane)
-{
-    // copy up to 64 queued leavers (ring positions head .. min(tail, head + 64))
-    const int n = min(64, tail - head);
-    if (lane < n) {
-        const int2 e = ring[(head + lane) & (kRing - 1)];
-        copy_particle(S, base + e.x, base + e.y, false, true);
-    }
-    head += n;
-}
+constexpr int kU = 16;    // 64-slot chunks per batch of code loads
+constexpr int kList = 64 * kU + 256;  // listed leavers of a wave (4 KB: 8 waves per SIMD fit)
 
 template <int ND, int NWV>
 struct CountSmem {
-    uint8_t kb[256];             // code -> key + 1 (0: the particle stays)
-    int wc[NWV][ND + 3];         // per wave: leavers of each key, then of all keys
-    int2 ring[NWV][kRing];       // per wave: (slot, staging slot) of queued leavers
+    uint8_t kb[256];              // code -> key + 1 (0: the particle stays)
+    int wc[NWV][ND + 3];          // per wave: leavers of each key, then of all keys
+    // per wave: listed leavers, slot (from the wave's first one, or in the batch) and key + 1
+    uint16_t slot[NWV][kList];
+    uint8_t key[NWV][kList];
 };
 
 // Leavers of patch p: per-key counts (kcnt, nleave), the vacated slots in
@@ -101,23 +94,39 @@ __device__ __forceinline__ void count_patch(const SimDev<T> &S, int p, int n, in
     const gptr_t<const uint8_t> code = glb((const uint8_t *)S.code) + base;
     const int per = ((n + kThreads - 1) / kThreads) * 64;
     const int lo = min(n, wave * per), hi = min(n, lo + per);
-    const bool one = hi - lo <= 64 * kU;
-    // codes of a batch, then keys + 1 of the batch, four 64-slot chunks per register
-    uint8_t t[kU];
-    uint32_t cw[kU / 4];
+    uint8_t t[kU];  // codes of a batch
     auto fetch = [&](int q0) {
         const gptr_t<const uint8_t> cp = code + q0 + lane;
         const int left = hi - q0 - lane;  // chunk u holds a slot while 64 u < left
 #pragma unroll
         for (int u = 0; u < kU; ++u) t[u] = 64 * u < left ? cp[64 * u] : uint8_t(ND / 2);
     };
-    auto translate = [&]() {
+    // append the leavers of batch q0 to the list of m entries, slots counted
+    // from `from`, and fetch the next batch; returns the entries then
+    uint16_t *lslot = sm.slot[wave];
+    uint8_t *lkey = sm.key[wave];
+    auto compact = [&](int q0, int from, int m) {
+        uint32_t cw[kU / 4];  // keys + 1, four 64-slot chunks per register
 #pragma unroll
         for (int u = 0; u < kU; u += 4)
             cw[u / 4] = (uint32_t)sm.kb[t[u]] | ((uint32_t)sm.kb[t[u + 1]] << 8) |
                         ((uint32_t)sm.kb[t[u + 2]] << 16) | ((uint32_t)sm.kb[t[u + 3]] << 24);
+        if (q0 + 64 * kU < hi) fetch(q0 + 64 * kU);
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (q0 + 64 * u >= hi) break;
+            const int kc = (int)((cw[u / 4] >> (8 * (u % 4))) & 0xffu);
+            const uint64_t b = __ballot(kc != 0);
+            if (kc) {
+                const int at = m + __popcll(b & lt);
+                lslot[at] = (uint16_t)(q0 - from + 64 * u + lane);
+                lkey[at] = (uint8_t)kc;
+            }
+            m += __popcll(b);
+        }
+        __builtin_amdgcn_wave_barrier();
+        return m;
     };
-    auto key1 = [&](int u) { return (int)((cw[u / 4] >> (8 * (u % 4))) & 0xffu); };
     fetch(lo);
     for (int e = tid; e < 256; e += kThreads) {
         int kb = 0;
@@ -128,88 +137,73 @@ __device__ __forceinline__ void count_patch(const SimDev<T> &S, int p, int n, in
     group_sync();
 
     // ---- walk 1: leavers per key in [lo, hi) ------------------------------
-    int cnt = 0;
+    int *wc = sm.wc[wave];
+    if (lane <= kKeys) wc[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    // the list of all batches is kept for walk 2 while it has room for
+    // another batch and slots fit 16 bits
+    bool kept = hi - lo <= 65536;
+    int m = 0, all = 0;
     for (int q0 = lo; q0 < hi; q0 += 64 * kU) {
-        if (q0 != lo) fetch(q0);
-        translate();
-#pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            if (q0 + 64 * u >= hi) break;
-            const int kc = key1(u);
-            uint64_t m = __ballot(kc != 0);
-            cnt += lane == kKeys ? __popcll(m) : 0;
-            while (m) {
-                const int kk = __builtin_amdgcn_readlane(kc, __ffsll((long long)m) - 1);
-                const uint64_t b = __ballot(kc == kk);
-                cnt += lane == kk - 1 ? __popcll(b) : 0;
-                m &= ~b;
-            }
+        if (!kept || m > kList - 64 * kU) {
+            kept = false;
+            m = 0;
         }
+        const int m0 = m;
+        m = compact(q0, kept ? lo : q0, m0);
+        all += m - m0;
+        for (int i = m0 + lane; i < m; i += 64) atomicAdd(&wc[lkey[i] - 1], 1);
+        __builtin_amdgcn_wave_barrier();
     }
-    if (lane <= kKeys) sm.wc[wave][lane] = cnt;
+    if (lane == kKeys) wc[kKeys] = all;
     group_sync();
 
     // ---- starting points: lane k of wave w holds the staging slot of the
     // next key-k leaver of the wave (key offset + earlier waves), lane kKeys
     // the next hole index ---------------------------------------------------
-    int run = 0;
-    if (lane <= kKeys) {
-        for (int w = 0; w < wave; ++w) run += sm.wc[w][lane];
-        if (lane < kKeys)
-            for (int kk = 0; kk < lane; ++kk)
-                for (int w = 0; w < NWV; ++w) run += sm.wc[w][kk];
+    int run = 0, tot = 0;
+    if (lane <= kKeys)
+        for (int w = 0; w < NWV; ++w) {
+            const int c = sm.wc[w][lane];
+            run += w < wave ? c : 0;
+            tot += c;
+        }
+    int incl = tot;
+#pragma unroll
+    for (int o = 1; o < 32; o <<= 1) {
+        const int y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
     }
+    if (lane < kKeys) run += incl - tot;
     if (wave == 0 && lane <= kKeys) {
-        int tot = 0;
-        for (int w = 0; w < NWV; ++w) tot += sm.wc[w][lane];
         if (lane < ND) glb(S.kcnt)[p * ND + lane] = tot;
         if (lane < kKeys) glb(S.kofs)[p * kKeys + lane] = run;  // wave 0: the key's offset
         if (lane == kKeys) glb(S.nleave)[p] = tot;
     }
 
-    // ---- walk 2: list holes, queue and copy staged leavers -----------------
-    if (__builtin_amdgcn_readlane(cnt, kKeys) > 0) {
-        int2 *ring = sm.ring[wave];
-        int head = 0, tail = 0;
-        for (int q0 = lo; q0 < hi; q0 += 64 * kU) {
-            if (!one) {
-                fetch(q0);
-                translate();
-            }
-#pragma unroll
-            for (int u = 0; u < kU; ++u) {
-                if (q0 + 64 * u >= hi) break;
-                const int kc = key1(u);
-                const int k = q0 + 64 * u + lane;
-                uint64_t m = __ballot(kc != 0);
-                if (!m) continue;
+    // ---- walk 2: list holes, copy staged leavers ---------------------------
+    if (all > 0) {
+        if (!kept) fetch(lo);
+        for (int q0 = lo; q0 < hi; q0 += kept ? hi - lo : 64 * kU) {
+            if (!kept) m = compact(q0, q0, 0);
+            for (int e0 = 0; e0 < m; e0 += 64) {
+                const bool has = e0 + lane < m;
+                const int kc = has ? lkey[e0 + lane] : 0, k = has ? q0 + lslot[e0 + lane] : 0;
                 const int h0 = __builtin_amdgcn_readlane(run, kKeys);
-                if (kc) glb(S.holes)[base + h0 + __popcll(m & lt)] = k;
-                run += lane == kKeys ? __popcll(m) : 0;
-                const uint64_t st = m & ~__ballot(kc == ND + 1);
+                if (has) glb(S.holes)[base + h0 + lane] = k;
+                run += lane == kKeys ? min(64, m - e0) : 0;
                 int dest = 0;
-                while (m) {
-                    const int kk = __builtin_amdgcn_readlane(kc, __ffsll((long long)m) - 1);
+                uint64_t todo = __ballot(has);
+                while (todo) {
+                    const int kk = __builtin_amdgcn_readlane(kc, __ffsll((long long)todo) - 1);
                     const uint64_t b = __ballot(kc == kk);
                     const int r0 = __builtin_amdgcn_readlane(run, kk - 1);
                     if (kc == kk) dest = r0 + __popcll(b & lt);
                     run += lane == kk - 1 ? __popcll(b) : 0;
-                    m &= ~b;
+                    todo &= ~b;
                 }
-                if (st) {
-                    if ((st >> lane) & 1)
-                        ring[(tail + __popcll(st & lt)) & (kRing - 1)] = make_int2(k, dest);
-                    tail += __popcll(st);
-                    __builtin_amdgcn_wave_barrier();
-                    if (tail - head >= 64) {
-                        drain_ring(S, base, ring, head, tail, lane);
-                        __builtin_amdgcn_wave_barrier();
-                    }
-                }
+                if (has && kc != ND + 1) copy_particle(S, base + k, base + dest, false, true);
             }
-        }
-        while (head < tail) {
-            drain_ring(S, base, ring, head, tail, lane);
             __builtin_amdgcn_wave_barrier();
         }
     }

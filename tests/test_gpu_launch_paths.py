@@ -219,6 +219,28 @@ def test_rebin_check_searches_any_number_of_vacated_slots(nd, moving):
     assert np.array_equal(g.perm(), ids[src])
 
 
+@pytest.mark.parametrize("ppc,moving", [(255, 0.005), (260, 0.005), (20, 0.05)])
+def test_rebin_of_patches_of_many_batches(ppc, moving):
+    # waves whose 65536 slots still fit a listed slot number, one more row, and
+    # lists of leavers near the room kept for them (256 per wave before the last batch)
+    _announce(f"re-binning of patches of {ppc * 1024} particles, {moving} of them leave")
+    wl = W.uniform_2d(n=(96, 32), patch=(32, 32), ppc=ppc)
+    from paper_1511_03878_amd.sim import Sim
+    g = Sim(wl["grid"], 32)
+    g.set_particles(wl["x"], wl["u"], wl["w"])
+    counts, ids = g.counts(), g.perm()
+    rng = np.random.default_rng(4)
+    codes = np.full(ids.size, 4, dtype=np.uint8)
+    go = rng.random(ids.size) < moving
+    codes[go] = rng.integers(0, 9, int(go.sum()))
+    owner = np.repeat(np.arange(counts.size), counts)
+    table = np.array([[neighbour_patch(p, c, [3, 1], (1, 1)) for c in range(9)] for p in range(3)])
+    newcount, src = oracle.rebin(counts, table[owner, codes].astype(np.int32))
+    g.rebin_codes(codes)
+    assert np.array_equal(g.counts(), newcount)
+    assert np.array_equal(g.perm(), ids[src])
+
+
 @pytest.mark.parametrize("precision", [32, 64])
 @pytest.mark.parametrize("n,patch", [((52, 20), (4, 20)), ((1000, 524), (50, 4)), ((1000, 525), (50, 25))])
 def test_fields_read_back_whole(n, patch, precision):
