@@ -291,6 +291,14 @@ struct BatchImpl : BatchBase {
     void build_tables();
     void refresh_member_views();
     QueueArgs queue_args() const;
+    // per member: the step in flight and a lower bound of its window jumps
+    // (empty: not known, every pass launches what any step may need)
+    struct Flight {
+        int64_t step, jumps;
+    };
+    std::vector<Flight> flight;
+    void set_flight(const std::vector<SimState> &states);
+    bool window_may_jump(size_t i);
     void launch_close_queue_pass();
     void launch_one_step();
     Timing &timing();

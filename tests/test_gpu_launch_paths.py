@@ -295,3 +295,26 @@ def test_charge_density_of_any_patch_shape(n, patch, precision):
     ref = rho_2d(x[0], x[1], w, -1.0, n) if len(n) == 2 else rho_3d(x, w, -1.0, n)
     got = g.field("rho")
     assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("start", [0, 9])
+def test_merges_and_jumps_are_launched_when_due(start):
+    # merges every 7 steps and a jump every 16: a run that stops for larger
+    # patches on the way and graph replays (whose launches serve any step)
+    # give the bits of single steps
+    _announce(f"window from step {start} and merges: long runs against single steps")
+    from tests.test_gpu_window import _gapped, _thermal_open
+    runs = []
+    for calls, kw in (((1,) * 80, {}), ((1, 20, 59), dict(capacity_factor=1.0, min_capacity=16)), ((80,), dict(graph=1))):
+        g = gpu_sim(_thermal_open(T_keV=5.0, ppc=9), 64, deterministic=1, **kw)
+        g.set_window(start, 1.0, (3, 3), _gapped())
+        g.set_merge(7, 8, 4)
+        for n in calls:
+            g.step(n)
+        d = g.diag()
+        assert d["window_cells"] >= 32 and d["merged"] > 0 and (d["relayouts"] > 0) == ("min_capacity" in kw)
+        runs.append([d["merged"], d["window_cells"], *(g.field(c) for c in FIELDS), g.counts(), *g.particles()[0],
+                     *g.particles()[1], g.perm()])
+    for r in runs[1:]:
+        for a, b in zip(runs[0], r):
+            assert np.array_equal(a, b)
