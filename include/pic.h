@@ -104,7 +104,7 @@ typedef struct {
     int32_t block;         /* threads per particle workgroup: 256, 512 or 1024; 0 = chosen, 256 or 512 */
     int32_t field_tile;    /* 2-D Yee update: 0 = strips by marching waves, 1..5 = tile shape presets */
     int32_t lane_stride;   /* particles between adjacent lanes of the particle kernel, 1..64;
-                              0 = 2 in 2-D, 4 in 3-D */
+                              0 = 2 in 2-D, 1 in 3-D */
     int32_t graph;         /* 1: step in batches of 32 replayed from a captured HIP graph
                               (when kernel timing is off); 0: plain launches */
     int32_t patch_order;   /* order of equal-size work items: 0 = patch id; 1 = the Hilbert

@@ -208,10 +208,11 @@ int validate_desc(const PicSimDesc &d, std::string &why)
 // Particles between adjacent lanes of the particle kernels (unless the
 // descriptor sets it).  2-D: 2, coalesced particle access outweighs fewer
 // same-address LDS atomics (stride 8 measured 1.5x slower on the laser box).
-// 3-D: 4, where each particle issues up to 144 window atomics and spreading
-// a wave over more cells pays (8^3-cell patches of the blob box, 512-thread
-// workgroups, two per CU: 22.55 ms per launch against 22.85 ms at stride 2).
-static int default_lane_stride(int nd) { return nd == 3 ? 4 : 2; }
+// 3-D: 1, whole lines per access (512 x 256 x 256 box 17.38 ms per step at
+// stride 4, 17.22 at 2, 17.09 at 1; 96 x 64 x 64 FP64 in 8 x 8 x 4 patches 405 /
+// 402 / 401 us; in 2-D stride 1 gains 1.5 % on the 1024 x 1024 thermal box and
+// loses 2.8 % on the 1536 x 384 laser box).
+static int default_lane_stride(int nd) { return nd == 3 ? 1 : 2; }
 
 // ---------------------------------------------------------------------------
 // SimImpl
