@@ -1908,6 +1908,7 @@ bool BatchImpl<T>::capture_graph()
     stream = capture_stream;
     std::vector<Flight> now;
     now.swap(flight);  // a graph serves any step
+    capturing = true;
     hipGraph_t g = nullptr;
     bool ok = hipStreamBeginCapture(capture_stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
     if (ok) {
@@ -1919,6 +1920,7 @@ bool BatchImpl<T>::capture_graph()
         ok = (hipStreamEndCapture(capture_stream, &g) == hipSuccess) && ok && g;
     }
     stream = user;
+    capturing = false;
     now.swap(flight);
     if (ok) ok = hipGraphInstantiate(&graph_exec, g, nullptr, nullptr, 0) == hipSuccess;
     if (g) (void)hipGraphDestroy(g);
@@ -2243,38 +2245,47 @@ void BatchImpl<T>::launch_one_step()
     Timing &tm = timing();
     ItemStamp *stamps = tm.stamp ? stamps_d : nullptr;
     if (stamps) launch_copy_int(nitems_d, stamp_n_d, stream);
+    const bool together = side_by_side && !(tm.enabled && tm.only < 0);
+    const bool fork = !together && ensure_side();
+    // The events that order the two streams complete with the kernels
+    // themselves: recorded behind them, each cost about 3 us (us per step,
+    // recorded / bound: 4096 x 1024 laser box 287 / 281, 1024 x 1024 428 / 422,
+    // 512 x 512 FP64 box in 8 x 8 patches 134.6 / 129.5, scan of 16 361 / 354.5).
+    // Timing has events of its own there; a graph records them.
+    const bool bound = fork && !tm.enabled && !ndet && !capturing;
+    const Ev2 pev = bound ? Ev2{nullptr, ev_fork} : tm.pair(1);
     if (nd == 3)
         launch_particles3d<T>(sims_d, items_d, nitems_d, head_d, grid_particles, block, maxP0, maxP1,
-                              maxP2, patch_const, stamps, stream, tm.pair(1));
+                              maxP2, patch_const, stamps, stream, pev);
     else
         launch_particles<T>(sims_d, items_d, nitems_d, head_d, grid_particles, block, maxP0, maxP1,
-                            patch_const, stamps, stream, tm.pair(1));
+                            patch_const, stamps, stream, pev);
     // deterministic members: fixed-point accumulators -> J[step & 1]
     if (ndet) launch_jfix<T>(sims_d, det_list_d, det_prefix_d, ndet, det_nodes, stream);
     // the field update (fields, currents, tile energies) and the re-binning
     // (particles, counts) touch disjoint data: run them side by side, in one
     // launch (small batches, unless every kernel group is timed) or on two
     // streams
-    if (side_by_side && !(tm.enabled && tm.only < 0)) {
+    if (together) {
         launch_fields_rebin<T>(sims_d, ns, tile_prefix_d, total_tiles, grid_maxwell, patch_prefix_d, total_patches,
                                grid_rebin, nd, hi_order, stream);
         launch_close_queue_pass();
         return;
     }
-    const bool fork = ensure_side();
     hipStream_t fs = stream;
     if (fork) {
-        hipcheck(hipEventRecord(ev_fork, stream), "fork");
+        if (!bound) hipcheck(hipEventRecord(ev_fork, stream), "fork");
         hipcheck(hipStreamWaitEvent(side_stream, ev_fork, 0), "fork");
         fs = side_stream;
     }
+    const Ev2 mev = bound ? Ev2{nullptr, ev_join} : tm.pair(2);
     if (nd == 3)
         launch_maxwell3d<T>(sims_d, ns, tile_prefix_d, total_tiles, grid_maxwell, yee_any, hi_order, fs,
-                            tm.pair(2));
+                            mev);
     else
         launch_maxwell<T>(sims_d, ns, tile_prefix_d, total_tiles, grid_maxwell, tile_preset, yee_any, hi_order,
-                          fs, tm.pair(2));
-    if (fork) hipcheck(hipEventRecord(ev_join, side_stream), "join");
+                          fs, mev);
+    if (fork && !bound) hipcheck(hipEventRecord(ev_join, side_stream), "join");
     launch_rebin<T>(sims_d, ns, patch_prefix_d, total_patches, grid_rebin, nd, stream, tm.pair(3));
     if (fork) hipcheck(hipStreamWaitEvent(stream, ev_join, 0), "join");
     launch_close_queue_pass();

@@ -282,6 +282,7 @@ struct BatchImpl : BatchBase {
     bool ensure_side();
     void free_graph();
     bool capture_graph();
+    bool capturing = false;
 
     explicit BatchImpl(hipStream_t s);
     ~BatchImpl() override;
