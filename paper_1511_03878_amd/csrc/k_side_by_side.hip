@@ -1,9 +1,8 @@
 // Field update and re-binning side by side in one launch, for small batches:
 // the first workgroups take the field strips or tiles, the others a pass of the
 // re-binning (the two share no data).  On two streams the fork and the join
-// cost about 7 and 6 us per step, as much as the passes of a small box
-// themselves (128 x 128 box: field update 10 us, re-binning 21 us); here they
-// cost nothing.  Yee: one launch with the count pass; sixth order: its three
+// cost about 7 us per step, as much as the passes of a small box themselves
+// (128 x 128 box: field update 6 us, re-binning 20 us); here they cost nothing.  Yee: one launch with the count pass; sixth order: its three
 // passes go with the count, check and scatter passes.
 #include <algorithm>
 

@@ -2092,11 +2092,12 @@ void BatchImpl<T>::build_tables()
     grid_rebin = std::max(1, std::min(total_patches, cu_count() * 16));
     // Small batches run the field update beside the re-binning in shared
     // launches instead of on a second stream, whose fork and join take about
-    // 13 us (two streams against shared launches, us per step: 64 x 64 box
-    // 51.5 / 41.1, 128 x 128 58.6 / 49.3, 1536 x 384 laser box 107.2 / 105.5,
-    // 96 x 64 x 64 448 / 448; 1024 x 1024 box 441 / 466, 256 x 128 x 128
-    // 2285 / 2350, where the check and scatter passes would wait for the
-    // field update).
+    // 7 us (two streams against shared launches, us per step: 64 x 64 FP64 box
+    // 43.7 / 37.6, 128 x 128 49.1 / 42.5, 460 x 180 66 / 57.4, sixth order
+    // 512 x 256 95 / 79, 1536 x 384 laser box 92.0 / 87.5, 64 x 48 x 40 154.7 /
+    // 153.0, 96 x 64 x 64 400 / 401; 1024 x 1024 box 436 / 451, scan of 16
+    // 361 / 383, 256 x 128 x 128 2285 / 2350, where the re-binning's passes lose
+    // occupancy to the field update's registers or wait for it).
     side_by_side = !(yee_any && hi_order) && tile_preset == 0 && total_patches <= 2048 && nodes <= kSideBySideNodes;
     if (std::getenv("PIC_LOG"))
         std::fprintf(stderr,
