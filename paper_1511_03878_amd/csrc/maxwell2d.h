@@ -304,13 +304,14 @@ __device__ __forceinline__ void yee2d_tiles(const SimDev<T> *__restrict__ sims, 
 // zero for them), so no access sits behind a branch.
 constexpr int kMarchAhead = 4;
 
-// Descriptor of a row of n nodes; offsets in bytes, kNoNode is past every row.
-constexpr uint32_t kNoNode = 0x80000000u;
+// Descriptor of a row of n nodes; offsets in bytes, kNoNode is past every row
+// (a grid has at most 2^30 cells and 4 rows or more: rows up to 2^31 + 8 bytes).
+constexpr uint32_t kNoNode = 0xfffffff0u;
 template <typename T>
 struct RowBuf {
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ RowBuf(const T *row, int n)
-        : r(__builtin_amdgcn_make_buffer_rsrc((void *)row, 0, n * (int)sizeof(T), 0x00027000))
+        : r(__builtin_amdgcn_make_buffer_rsrc((void *)row, 0, (int)((uint32_t)n * (uint32_t)sizeof(T)), 0x00027000))
     {
     }
     __device__ __forceinline__ T load(uint32_t off) const
