@@ -2196,17 +2196,24 @@ template <typename T>
 void BatchImpl<T>::launch_close_queue_pass()
 {
     // merges, then window jumps, of the steps that close in this pass (not
-    // launched where the step in flight is known to have none)
+    // launched where no step closes or the one that does is known to have none)
+    const bool known = !flight.empty();
     for (size_t i = 0; i < members.size(); ++i)
         if (members[i]->merge_every > 0 && members[i]->cap_d &&
-            (flight.empty() || (flight[i].step + 1) % members[i]->merge_every == 0))
+            (!known || (flight[i].closes && (flight[i].step + 1) % members[i]->merge_every == 0)))
             launch_merge<T>(sims_d + i, members[i]->npatch, 0, 0, 0, members[i]->merge_cmax, stream);
-    for (size_t i = 0; i < members.size(); ++i)
-        if (members[i]->win_on && members[i]->cap_d && window_may_jump(i))
-            launch_window<T>(sims_d + i, members[i]->fn[1], members[i]->np[1], stream);
+    for (size_t i = 0; i < members.size(); ++i) {
+        if (!members[i]->win_on || !members[i]->cap_d) continue;
+        const Jump j = known ? window_jump(i) : Jump::maybe;
+        if (j != Jump::no) launch_window<T>(sims_d + i, members[i]->fn[1], members[i]->np[1], stream);
+        if (j == Jump::yes) ++flight[i].jumps;
+    }
     launch_close_queue<T>(sims_d, queue_args(), stream, timing().pair(0));
     hipcheck(hipGetLastError(), "queue launch");
-    for (Flight &f : flight) ++f.step;
+    for (Flight &f : flight) {
+        f.step += f.closes;
+        f.closes = false;
+    }
 }
 
 // The member states as read: the step in flight and the jumps of the next
@@ -2216,26 +2223,25 @@ template <typename T>
 void BatchImpl<T>::set_flight(const std::vector<SimState> &states)
 {
     flight.clear();
-    for (const SimState &s : states) flight.push_back({s.step, s.wshift});
+    for (const SimState &s : states)
+        flight.push_back({s.step, s.wshift, s.active && s.rebinned && !(s.flags & kFlagPending)});
 }
 
-// Whether member i's window may jump at the end of the step in flight.  The
-// kernel decides; this is its test with a margin for rounding.  (1536 x 384
-// laser box, a merge every 100 steps and a jump every 45: 4.7 us per step for
-// each of the two kernels that then had nothing to do.)
+// Whether member i's window jumps in the next close pass.  The kernel decides;
+// this is its test with a margin for rounding.  (1536 x 384 laser box, a merge
+// every 100 steps and a jump every 45: 4.7 us per step for each of the two
+// kernels that then had nothing to do.)
 template <typename T>
-bool BatchImpl<T>::window_may_jump(size_t i)
+typename BatchImpl<T>::Jump BatchImpl<T>::window_jump(size_t i) const
 {
-    if (flight.empty()) return true;
     const SimImpl<T> &m = *members[i];
-    Flight &f = flight[i];
+    const Flight &f = flight[i];
     const int64_t n = f.step + 1 - m.win_start;
-    if (n <= 0) return false;
+    if (!f.closes || n <= 0) return Jump::no;
     const double due = m.win_v * (double)n * m.desc.dt / ((double)m.P[0] * m.desc.d[0]);
     const double eps = 1e-9 * (1.0 + due);
-    if (std::floor(due + eps) <= (double)f.jumps) return false;
-    if (std::floor(due - eps) > (double)f.jumps) ++f.jumps;
-    return true;
+    if (std::floor(due + eps) <= (double)f.jumps) return Jump::no;
+    return std::floor(due - eps) > (double)f.jumps ? Jump::yes : Jump::maybe;
 }
 
 // One step pass: particles, Yee, re-binning, then close + next queue.
@@ -2243,6 +2249,7 @@ template <typename T>
 void BatchImpl<T>::launch_one_step()
 {
     const int ns = (int)members.size();
+    for (Flight &f : flight) f.closes = true;
     Timing &tm = timing();
     ItemStamp *stamps = tm.stamp ? stamps_d : nullptr;
     if (stamps) launch_copy_int(nitems_d, stamp_n_d, stream);
@@ -2335,12 +2342,9 @@ int BatchImpl<T>::run(int64_t max_steps, bool until_done, const SimState *known)
     const int64_t K = kGraphSteps;
     int finished = 0;
     set_flight(last);
-    launch_close_queue_pass();  // queue of the first step
-    // (it closes no step, except one whose re-binning is done already)
-    for (size_t i = 0; i < members.size(); ++i) {
-        const SimState &s = last[i];
-        if (!(s.active && s.rebinned && !(s.flags & kFlagPending))) --flight[i].step;
-    }
+    // queue of the first step (closes no step, except one whose re-binning is
+    // done already)
+    launch_close_queue_pass();
     for (;;) {
         // never launch more passes than the largest budget still needs
         int64_t todo = std::min<int64_t>(K, budget);
@@ -2378,6 +2382,7 @@ int BatchImpl<T>::run(int64_t max_steps, bool until_done, const SimState *known)
             refresh_member_views();
             if (dirty) build_tables();
             // close the recovered steps and queue the next step for everyone
+            set_flight(read_states());
             launch_close_queue_pass();
             budget = 0;
             any_left = false;

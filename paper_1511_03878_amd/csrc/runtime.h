@@ -292,14 +292,18 @@ struct BatchImpl : BatchBase {
     void build_tables();
     void refresh_member_views();
     QueueArgs queue_args() const;
-    // per member: the step in flight and a lower bound of its window jumps
-    // (empty: not known, every pass launches what any step may need)
+    // per member: completed steps, a lower bound of its window jumps and
+    // whether the next close pass closes a step (empty: not known, every pass
+    // launches what any step may need); only a pass that closes a step counts it
+    // and its jump
     struct Flight {
         int64_t step, jumps;
+        bool closes;
     };
+    enum class Jump { no, maybe, yes };
     std::vector<Flight> flight;
     void set_flight(const std::vector<SimState> &states);
-    bool window_may_jump(size_t i);
+    Jump window_jump(size_t i) const;
     void launch_close_queue_pass();
     void launch_one_step();
     Timing &timing();

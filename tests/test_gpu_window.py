@@ -190,3 +190,65 @@ def test_window_with_merging_and_curve_order_fp64():
     assert o.window_shift >= 1 and o.merged > 0
     _check_fp64(g, o)
     assert g.diag()["merged"] == o.merged
+
+
+@pytest.mark.parametrize("start,velocity", [(0, 1.0), (5, 0.97)])
+def test_window_jumps_when_due_however_steps_are_split(start, velocity):
+    """A jump interval that is no whole number of steps: one call, single
+    steps, calls that begin or end on a step with a jump, a batch and graph
+    replays jump on the same steps as the oracle and give the same bits."""
+    _announce(f"window from step {start} at speed {velocity}: jumps in differently split runs")
+    from paper_1511_03878_amd.sim import Batch
+    wl = _thermal_open(seed=7)
+    wl["grid"] = dict(wl["grid"], dt=W.cfl_dt(wl["grid"]["d"]))  # 11.9 steps per jump at v = 1
+    steps, win = 60, (start, velocity, (2, 2), _gapped())
+    o = _pair(wl, 64, win)[1]
+    shift = [0]
+    for _ in range(steps):
+        o.step(1)
+        shift.append(o.window_shift)
+    assert shift[-1] >= 4
+    due = [k for k in range(1, steps + 1) if shift[k] > shift[k - 1]]
+    runs = []
+
+    def done(g, k):
+        assert g.diag()["window_cells"] == shift[k] * 8, k
+
+    def result(g):
+        runs.append([*(g.field(c) for c in ("Ex", "Ey", "Ez", "Bx", "By", "Bz", "Jx", "Jy", "Jz")), g.counts(),
+                     *g.particles()[0], *g.particles()[1], g.perm()])
+
+    # (a call whose first step jumps, one whose last step does)
+    for calls in ((steps,), (1,) * steps, (due[0] - 1, steps - due[0] + 1), (due[0], due[1] - 1 - due[0], 1, 25)):
+        g = gpu_sim(wl, 64, deterministic=1)
+        g.set_window(*win)
+        k = 0
+        for n in calls:
+            g.step(n)
+            k += n
+            done(g, k)
+        if k < steps:
+            g.step(steps - k)
+            done(g, steps)
+        result(g)
+    _check_fp64(g, o)
+    g = gpu_sim(wl, 64, deterministic=1, graph=1)
+    g.set_window(*win)
+    for n in (due[0] - 1, steps - due[0] + 1):
+        g.step(n)
+    done(g, steps)
+    result(g)
+    # a batch that stops every 16 and every 4 steps
+    for per in (16, 4):
+        g = gpu_sim(wl, 64, deterministic=1)
+        g.set_window(*win)
+        b = Batch(64)
+        b.add(g, steps)
+        for k in range(per, steps + per, per):
+            b.step(per)
+            done(g, min(k, steps))
+        b.close()
+        result(g)
+    for r in runs[1:]:
+        for x, y in zip(runs[0], r):
+            assert np.array_equal(x, y)
