@@ -245,7 +245,7 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
             s_loud[slot ^ 1] = s_dep[slot ^ 1] = 0;
         }
         const bool quiet = __builtin_amdgcn_readfirstlane(s_loud[slot]) == 0;
-        bool dep = false;
+        bool dep = false;  // a particle of this lane deposited
 
         // Particles at rest in a patch without fields (the plasma ahead of a
         // laser pulse) stay as they are: up to the wave's first unit with a
@@ -343,7 +343,7 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
                 const double az = (double)q * qw * (double)(uz * ig1) * fs;
                 const bool inplane = dxl != T(0) || dyl != T(0);
                 const bool deposits = inplane || az != 0.0;
-                dep |= __any(deposits) != 0;
+                dep |= deposits;
                 if (deposits) {
                     int mx, my;
                     double S0x[4], DSx[4], S0y[4], DSy[4];
@@ -441,7 +441,9 @@ __global__ __launch_bounds__(BLOCK, (BLOCK == 512 && sizeof(T) == 4) ? 4 : 1) vo
         // the re-binning scans only patches that may have leavers
         if (__ballot(left) && ln == 0) *glb(S.moved + p) = 1;
         if (err) __hip_atomic_fetch_or(&glb(S.st)->flags, err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (dep && ln == 0) s_dep[slot] = 1;
+        // (asked of the whole wave: a lane whose particle has no valid move never
+        // reached the deposit)
+        if (__any(dep) && ln == 0) s_dep[slot] = 1;
         __syncthreads();
 
         // ---- flush and clear the current tile ----------------------------------

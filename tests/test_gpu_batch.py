@@ -168,3 +168,42 @@ def test_served_results_match_the_oracle_and_growth_is_charged():
             assert rel_l2(r.result["fields"], ref) < 1e-5
         Wg = r.result["U"] + r.result["K"]
         assert np.abs(Wg - np.array(Wo)).max() <= 1e-3 * max(np.abs(Wo).max(), 1e-300)
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+def test_member_with_bad_particles_leaves_the_others_alone(precision):
+    # the first particle of every patch of one member has no finite momentum:
+    # the member stops, and the current the rest of its items deposited must not
+    # reach the items of the other member that the same workgroups take next
+    # (fewer particles per patch, so later in the queue)
+    print(f"[gpu-test] batch with a failing member, 4096 patches each, fp{precision}", flush=True)
+    from paper_1511_03878_amd.sim import Batch, Sim
+    n, patch, d = (512, 512), (8, 8), (0.1, 0.1)
+    grid = dict(ndim=2, n=list(n), d=list(d), dt=W.cfl_dt(d), patch=list(patch), periodic=[1, 1], q=-1.0, m=1.0)
+
+    def load(per_patch, bad, seed):
+        rng = np.random.default_rng(seed)
+        npatch = 64 * 64
+        org = np.repeat(np.arange(npatch), per_patch)
+        x = [8.0 * (org % 64) + 8.0 * rng.random(org.size), 8.0 * (org // 64) + 8.0 * rng.random(org.size)]
+        u = [0.1 * rng.standard_normal(org.size) for _ in range(3)]
+        if bad:
+            u[0][::per_patch] = np.nan
+        g = Sim(grid, precision, deterministic=1)
+        g.set_particles(x, u, np.full(org.size, 0.25))
+        return g
+
+    alone = load(30, False, 2)
+    alone.step(3)
+    bad, good = load(40, True, 1), load(30, False, 2)
+    b = Batch(precision)
+    b.add(bad, 3)
+    b.add(good, 3)
+    b.step(3)
+    b.close()
+    assert bad.diag()["flags"] & 2 and good.diag()["flags"] == 0 and good.diag()["step"] == 3
+    for c in ("Ex", "Ey", "Ez", "Bx", "By", "Bz", "Jx", "Jy", "Jz"):
+        assert np.array_equal(alone.field(c), good.field(c)), c
+    assert np.array_equal(alone.perm(), good.perm())
+    for p, q in zip([*alone.particles()[0], *alone.particles()[1]], [*good.particles()[0], *good.particles()[1]]):
+        assert np.array_equal(p, q)
