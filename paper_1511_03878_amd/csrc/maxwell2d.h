@@ -57,14 +57,8 @@ __device__ __forceinline__ int xcd_block(int b, int g)
     return (g & 7) ? b : (b & 7) * (g >> 3) + (b >> 3);
 }
 
-// The updates with two products, and the Silver-Mueller ghosts, in one stated
-// fused form, so the tiles and the strips below give the same bits:
-// a p - b q, and the ghosts at x = 0 (E face values, B first inside) and x = L.
-template <typename T>
-__device__ __forceinline__ T curl2(T a, T p, T b, T q)
-{
-    return fma(a, p, -(b * q));
-}
+// The Silver-Mueller ghosts in one stated form (see curl2), at x = 0 (E face
+// values, B first inside) and x = L.
 template <typename T>
 __device__ __forceinline__ T ghost_lo_bz(T ey, T b, T eyi, T r, T ir)
 {
@@ -430,7 +424,7 @@ __device__ __forceinline__ void yee2d_march(const SimDev<T> *__restrict__ sims, 
             }
             double en = 0.0;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) en += (double)c.e[k] * (double)c.e[k] + (double)c.b[k] * (double)c.b[k];
+            for (int k = 0; k < 3; ++k) en += squares2((double)c.e[k], (double)c.b[k]);
             esum += own && b <= rows ? en : 0.0;
         };
         // E^{n+1} of the row in c from B^{n+1/2} of it (bh) and of the previous row
@@ -526,13 +520,13 @@ __device__ __forceinline__ void hi2d_tiles(const SimDev<T> *__restrict__ sims, i
             // (half point before it) along x (ax = 0) or y (ax = 1)
             auto dfw = [&](const T *f, int ax) {
                 const int u = ax == 0, v = ax == 1;
-                return c1 * (node(f, u, v) - node(f, 0, 0)) + c2 * (node(f, 2 * u, 2 * v) - node(f, -u, -v)) +
-                       c3 * (node(f, 3 * u, 3 * v) - node(f, -2 * u, -2 * v));
+                return sum3(c1, node(f, u, v) - node(f, 0, 0), c2, node(f, 2 * u, 2 * v) - node(f, -u, -v), c3,
+                            node(f, 3 * u, 3 * v) - node(f, -2 * u, -2 * v));
             };
             auto dbw = [&](const T *f, int ax) {
                 const int u = ax == 0, v = ax == 1;
-                return c1 * (node(f, 0, 0) - node(f, -u, -v)) + c2 * (node(f, u, v) - node(f, -2 * u, -2 * v)) +
-                       c3 * (node(f, 2 * u, 2 * v) - node(f, -3 * u, -3 * v));
+                return sum3(c1, node(f, 0, 0) - node(f, -u, -v), c2, node(f, u, v) - node(f, -2 * u, -2 * v), c3,
+                            node(f, 2 * u, 2 * v) - node(f, -3 * u, -3 * v));
             };
             if constexpr (PASS == 0 || PASS == 2) {
                 T *const *E = PASS == 0 ? Fc : Fn;
@@ -541,11 +535,10 @@ __device__ __forceinline__ void hi2d_tiles(const SimDev<T> *__restrict__ sims, i
                 const T bz0 = glb(PASS == 0 ? Fc[5] : Fn[5])[k];
                 const T bx = bx0 - h * dfw(E[2], 1) * iy;
                 const T by = by0 + h * dfw(E[2], 0) * ix;
-                const T bz = bz0 - h * (dfw(E[1], 0) * ix - dfw(E[0], 1) * iy);
+                const T bz = bz0 - h * curl2(dfw(E[1], 0), ix, dfw(E[0], 1), iy);
                 if constexpr (PASS == 0) {
                     const T ex = glb(Fc[0])[k], ey = glb(Fc[1])[k], ez = glb(Fc[2])[k];
-                    esum += (double)ex * ex + (double)ey * ey + (double)ez * ez + (double)bx0 * bx0 +
-                            (double)by0 * by0 + (double)bz0 * bz0;
+                    esum += squares6(ex, ey, ez, bx0, by0, bz0);
                 }
                 glb(Fn[3])[k] = bx;
                 glb(Fn[4])[k] = by;
@@ -555,7 +548,7 @@ __device__ __forceinline__ void hi2d_tiles(const SimDev<T> *__restrict__ sims, i
                 T *const *Jn = S.J[(stepn + 1) & 1];
                 const T ex = glb(Fc[0])[k] + dt * (dbw(Fn[5], 1) * iy - glb(Jc[0])[k]);
                 const T ey = glb(Fc[1])[k] + dt * (-dbw(Fn[5], 0) * ix - glb(Jc[1])[k]);
-                const T ez = glb(Fc[2])[k] + dt * (dbw(Fn[4], 0) * ix - dbw(Fn[3], 1) * iy - glb(Jc[2])[k]);
+                const T ez = glb(Fc[2])[k] + dt * (curl2(dbw(Fn[4], 0), ix, dbw(Fn[3], 1), iy) - glb(Jc[2])[k]);
                 glb(Fn[0])[k] = ex;
                 glb(Fn[1])[k] = ey;
                 glb(Fn[2])[k] = ez;

@@ -72,8 +72,8 @@ __device__ __forceinline__ T d6(const gptr_t<const T> f, int64_t k, int64_t stri
         return f[k + (int64_t)(ii - i) * stride];
     };
     const T c1 = T(75.0 / 64.0), c2 = T(-25.0 / 384.0), c3 = T(3.0 / 640.0);
-    return fwd ? c1 * (at(1) - at(0)) + c2 * (at(2) - at(-1)) + c3 * (at(3) - at(-2))
-               : c1 * (at(0) - at(-1)) + c2 * (at(1) - at(-2)) + c3 * (at(2) - at(-3));
+    return fwd ? sum3(c1, at(1) - at(0), c2, at(2) - at(-1), c3, at(3) - at(-2))
+               : sum3(c1, at(0) - at(-1), c2, at(1) - at(-2), c3, at(2) - at(-3));
 }
 
 // pass 1 (PASS = 0) and pass 3 (PASS = 2): B -= h curl E
@@ -107,8 +107,7 @@ __device__ __forceinline__ void hi3d_b_tiles(const SimDev<T> *__restrict__ sims,
             const T bx = glb((const T *)Bsrc[3])[k], by = glb((const T *)Bsrc[4])[k],
                     bz = glb((const T *)Bsrc[5])[k];
             if (PASS == 0) {
-                esum = (double)ex * ex + (double)ey * ey + (double)ez * ez + (double)bx * bx +
-                       (double)by * by + (double)bz * bz;
+                esum = squares6(ex, ey, ez, bx, by, bz);
             }
             if (S.morder == 6) {
                 const int i = (int)(k % fn0), j = (int)((k / fn0) % fn1), l = (int)(k / ((int64_t)fn0 * fn1));
@@ -116,9 +115,9 @@ __device__ __forceinline__ void hi3d_b_tiles(const SimDev<T> *__restrict__ sims,
                 auto dx = [&](gptr_t<const T> f) { return d6<T>(f, k, 1, i, fn0, true); };
                 auto dy = [&](gptr_t<const T> f) { return d6<T>(f, k, sy, j, fn1, true); };
                 auto dz = [&](gptr_t<const T> f) { return d6<T>(f, k, sz, l, fn2, true); };
-                glb(Fn[3])[k] = bx - h * (dy(Ez) * iy - dz(Ey) * iz);
-                glb(Fn[4])[k] = by - h * (dz(Ex) * iz - dx(Ez) * ix);
-                glb(Fn[5])[k] = bz - h * (dx(Ey) * ix - dy(Ex) * iy);
+                glb(Fn[3])[k] = bx - h * curl2(dy(Ez), iy, dz(Ey), iz);
+                glb(Fn[4])[k] = by - h * curl2(dz(Ex), iz, dx(Ez), ix);
+                glb(Fn[5])[k] = bz - h * curl2(dx(Ey), ix, dy(Ex), iy);
             } else {
                 glb(Fn[3])[k] = bx - h * ((Ez[nd.jp] - ez) * iy - (Ey[nd.kp] - ey) * iz);
                 glb(Fn[4])[k] = by - h * ((Ex[nd.kp] - ex) * iz - (Ez[nd.ip] - ez) * ix);
@@ -171,9 +170,9 @@ __device__ __forceinline__ void hi3d_e_tiles(const SimDev<T> *__restrict__ sims,
             auto dx = [&](gptr_t<const T> f) { return d6<T>(f, k, 1, i, fn0, false); };
             auto dy = [&](gptr_t<const T> f) { return d6<T>(f, k, sy, j, fn1, false); };
             auto dz = [&](gptr_t<const T> f) { return d6<T>(f, k, sz, l, fn2, false); };
-            glb(Fn[0])[k] = glb((const T *)Fc[0])[k] + dt * (dy(Bz) * iy - dz(By) * iz - glb((const T *)Jc[0])[k]);
-            glb(Fn[1])[k] = glb((const T *)Fc[1])[k] + dt * (dz(Bx) * iz - dx(Bz) * ix - glb((const T *)Jc[1])[k]);
-            glb(Fn[2])[k] = glb((const T *)Fc[2])[k] + dt * (dx(By) * ix - dy(Bx) * iy - glb((const T *)Jc[2])[k]);
+            glb(Fn[0])[k] = glb((const T *)Fc[0])[k] + dt * (curl2(dy(Bz), iy, dz(By), iz) - glb((const T *)Jc[0])[k]);
+            glb(Fn[1])[k] = glb((const T *)Fc[1])[k] + dt * (curl2(dz(Bx), iz, dx(Bz), ix) - glb((const T *)Jc[1])[k]);
+            glb(Fn[2])[k] = glb((const T *)Fc[2])[k] + dt * (curl2(dx(By), ix, dy(Bx), iy) - glb((const T *)Jc[2])[k]);
             glb(Jn[0])[k] = T(0);
             glb(Jn[1])[k] = T(0);
             glb(Jn[2])[k] = T(0);
@@ -304,11 +303,10 @@ __device__ __forceinline__ void yee3d_blocks(const SimDev<T> *__restrict__ sims,
                     const T bx = sB[bs][0][i], by = sB[bs][1][i], bz = sB[bs][2][i];
                     if (own_plane && lx >= 1 && lx <= kYee3X && ly >= 1 && ly <= kYee3Y && x0 + lx < fn0 &&
                         y0 + ly < fn1)
-                        esum += (double)ex * ex + (double)ey * ey + (double)ez * ez + (double)bx * bx +
-                                (double)by * by + (double)bz * bz;
-                    sB[bs][0][i] = bx - h * ((sE[ec][2][e + kEX] - ez) * iy - (sE[en][1][e] - ey) * iz);
-                    sB[bs][1][i] = by - h * ((sE[en][0][e] - ex) * iz - (sE[ec][2][e + 1] - ez) * ix);
-                    sB[bs][2][i] = bz - h * ((sE[ec][1][e + 1] - ey) * ix - (sE[ec][0][e + kEX] - ex) * iy);
+                        esum += squares6(ex, ey, ez, bx, by, bz);
+                    sB[bs][0][i] = bx - h * curl2(sE[ec][2][e + kEX] - ez, iy, sE[en][1][e] - ey, iz);
+                    sB[bs][1][i] = by - h * curl2(sE[en][0][e] - ex, iz, sE[ec][2][e + 1] - ez, ix);
+                    sB[bs][2][i] = bz - h * curl2(sE[ec][1][e + 1] - ey, ix, sE[ec][0][e + kEX] - ex, iy);
                 }
             }
         };
@@ -321,9 +319,9 @@ __device__ __forceinline__ void yee3d_blocks(const SimDev<T> *__restrict__ sims,
                     const int lx = j % kE2X + 1, ly = j / kE2X + 1;
                     const int e = ly * kEX + lx, b = ly * kBX + lx;
                     const T bx = sB[bc][0][b], by = sB[bc][1][b], bz = sB[bc][2][b];
-                    sE[es][0][e] = sE[es][0][e] + dt * ((bz - sB[bc][2][b - kBX]) * iy - (by - sB[bp][1][b]) * iz - jr[0][r]);
-                    sE[es][1][e] = sE[es][1][e] + dt * ((bx - sB[bp][0][b]) * iz - (bz - sB[bc][2][b - 1]) * ix - jr[1][r]);
-                    sE[es][2][e] = sE[es][2][e] + dt * ((by - sB[bc][1][b - 1]) * ix - (bx - sB[bc][0][b - kBX]) * iy - jr[2][r]);
+                    sE[es][0][e] += dt * (curl2(bz - sB[bc][2][b - kBX], iy, by - sB[bp][1][b], iz) - jr[0][r]);
+                    sE[es][1][e] += dt * (curl2(bx - sB[bp][0][b], iz, bz - sB[bc][2][b - 1], ix) - jr[1][r]);
+                    sE[es][2][e] += dt * (curl2(by - sB[bc][1][b - 1], ix, bx - sB[bc][0][b - kBX], iy) - jr[2][r]);
                 }
             }
         };
@@ -341,9 +339,9 @@ __device__ __forceinline__ void yee3d_blocks(const SimDev<T> *__restrict__ sims,
                 const int e = ly * kEX + lx, b = ly * kBX + lx;
                 const T ex = sE[ec][0][e], ey = sE[ec][1][e], ez = sE[ec][2][e];
                 const int64_t g = ((int64_t)z * fn1 + (y0 + ly)) * fn0 + (x0 + lx);
-                B0[g] = sB[bc][0][b] - h * ((sE[ec][2][e + kEX] - ez) * iy - (sE[en][1][e] - ey) * iz);
-                B1[g] = sB[bc][1][b] - h * ((sE[en][0][e] - ex) * iz - (sE[ec][2][e + 1] - ez) * ix);
-                B2[g] = sB[bc][2][b] - h * ((sE[ec][1][e + 1] - ey) * ix - (sE[ec][0][e + kEX] - ex) * iy);
+                B0[g] = sB[bc][0][b] - h * curl2(sE[ec][2][e + kEX] - ez, iy, sE[en][1][e] - ey, iz);
+                B1[g] = sB[bc][1][b] - h * curl2(sE[en][0][e] - ex, iz, sE[ec][2][e + 1] - ez, ix);
+                B2[g] = sB[bc][2][b] - h * curl2(sE[ec][1][e + 1] - ey, ix, sE[ec][0][e + kEX] - ex, iy);
                 E0[g] = ex;
                 E1[g] = ey;
                 E2[g] = ez;

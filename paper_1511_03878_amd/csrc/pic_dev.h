@@ -247,6 +247,28 @@ __device__ __forceinline__ int find_sim(const int *prefix, int nsims, int g)
     return lo;
 }
 
+// ---- sums of products in a stated form ---------------------------------------
+// The field bodies are compiled into several kernels (alone, beside a pass of
+// the re-binning, strips and tiles), which have to give the same bits.  Which
+// product of a sum of two the compiler rounds by itself depends on the code around
+// it, so the forms are written out.  a p - b q:
+template <typename T>
+__device__ __forceinline__ T curl2(T a, T p, T b, T q)
+{
+    return fma(a, p, -(b * q));
+}
+// a p + b q + c r
+template <typename T>
+__device__ __forceinline__ T sum3(T a, T p, T b, T q, T c, T r)
+{
+    return fma(c, r, fma(a, p, b * q));
+}
+// a a + b b in FP64, and the squares of E and B
+__device__ __forceinline__ double squares2(double a, double b) { return fma(a, a, b * b); }
+__device__ __forceinline__ double squares6(double ex, double ey, double ez, double bx, double by, double bz)
+{
+    return fma(bz, bz, fma(by, by, fma(bx, bx, fma(ez, ez, squares2(ex, ey)))));
+}
 
 // ---- fixed-point current ---------------------------------------------------
 // Current tiles accumulate integers: a contribution c enters as round(c 2^s)

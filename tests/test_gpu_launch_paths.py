@@ -318,3 +318,34 @@ def test_merges_and_jumps_are_launched_when_due(start):
     for r in runs[1:]:
         for a, b in zip(runs[0], r):
             assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision", [32, 64])
+@pytest.mark.parametrize("case", ["2d_open", "2d_sixth", "3d", "3d_sixth"])
+def test_alone_and_beside_a_large_box_give_the_same_bits(case, precision):
+    # alone the field update shares launches with the re-binning, beside a grid
+    # of more than 3 * 2^18 nodes it has kernels of its own on a second stream
+    _announce(f"shared launches alone against separate ones in a large batch: {case} fp{precision}")
+    from paper_1511_03878_amd.sim import Batch, Sim
+    wl, kw = _box(case)
+    nd = wl["grid"]["ndim"]
+    n, patch = ([1024, 1024], [64, 8]) if nd == 2 else ([128, 96, 80], [8, 8, 8])
+    runs = []
+    for together in (False, True):
+        g = gpu_sim(wl, precision, deterministic=1, **kw)
+        if together:
+            d = [0.1] * nd
+            big = Sim(dict(ndim=nd, n=n, d=d, dt=0.5 * W.cfl_dt(d), patch=patch, periodic=[1] * nd), precision, **kw)
+            x = [np.full(3, 0.5 * v) for v in n]
+            big.set_particles(x, [np.zeros(3)] * 3, np.full(3, 0.1))
+            b = Batch(precision, ndim=nd)
+            b.add(g, 12)
+            b.add(big, 12)
+            b.step(12)
+            b.close()
+        else:
+            g.step(12)
+        runs.append([g.field(c) for c in FIELDS] + [g.history(0, 12)[0], g.counts(), *g.particles()[0],
+                                                    *g.particles()[1], g.perm()])
+    for a, b in zip(*runs):
+        assert np.array_equal(a, b)
