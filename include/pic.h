@@ -392,7 +392,8 @@ int pic_history_get(PicSim *s, int64_t first, int64_t n, double *U, double *K, i
  * non-NULL `cache` path the result is stored in that text file under a key
  * of dimensions, precision, grid, patch shape and particle count (to a
  * factor of two); a later call with the same key applies the stored
- * settings without running.  `out` (may be NULL) receives the settings in
+ * settings without running.  Choices stored by a version of the library whose
+ * settings meant something else are passed over.  `out` (may be NULL) receives the settings in
  * effect.  Not for members of a batch (PIC_ESTATE). */
 typedef struct {
     int32_t block, field_tile, lane_stride, chunk;

@@ -1523,6 +1523,12 @@ void SimImpl<T>::state_load(const void *blob, size_t size)
 // ---------------------------------------------------------------------------
 // launch-setting tuner
 
+// Part of the cache keys, raised when a setting's meaning, a default or a kernel
+// that the tuner times changes: a choice stored before is then not taken (one of
+// version 1 would keep a box on field tiles, which the strips of field_tile 0
+// have overtaken, and off the shared launches).
+constexpr int kTuneVersion = 2;
+
 template <typename T>
 void SimImpl<T>::autotune(int steps, const char *cache, PicTuneResult *out)
 {
@@ -1532,8 +1538,8 @@ void SimImpl<T>::autotune(int steps, const char *cache, PicTuneResult *out)
     int bucket = 0;
     while (((int64_t)1 << bucket) < std::max<int64_t>(live, 1)) ++bucket;
     char key[160];
-    std::snprintf(key, sizeof(key), "pic-tune nd=%d prec=%d n=%d,%d,%d patch=%d,%d,%d np2=%d", nd, precision,
-                  n[0], n[1], n[2], P[0], P[1], P[2], bucket);
+    std::snprintf(key, sizeof(key), "pic-tune v%d nd=%d prec=%d n=%d,%d,%d patch=%d,%d,%d np2=%d", kTuneVersion,
+                  nd, precision, n[0], n[1], n[2], P[0], P[1], P[2], bucket);
     struct Cfg {
         int block, field_tile, lane_stride, chunk;
     };
@@ -1623,8 +1629,8 @@ void autotune_patch(PicSimDesc &d, const PicSpeciesDesc &sp, const PicLaserDesc 
     if (!cand || ncand <= 0) throw Error(PIC_EINVAL, "no candidates");
     const int nd = d.ndim;
     char key[200];
-    std::snprintf(key, sizeof(key), "pic-patch nd=%d prec=%d n=%d,%d,%d profile=%d load=%d ppc=%d", nd,
-                  d.precision, d.n[0], d.n[1], nd == 3 ? d.n[2] : 1, sp.profile, sp.loading, sp.ppc);
+    std::snprintf(key, sizeof(key), "pic-patch v%d nd=%d prec=%d n=%d,%d,%d profile=%d load=%d ppc=%d", kTuneVersion,
+                  nd, d.precision, d.n[0], d.n[1], nd == 3 ? d.n[2] : 1, sp.profile, sp.loading, sp.ppc);
     PicTuneResult res;
     std::memset(&res, 0, sizeof(res));
     if (cache) {

@@ -32,3 +32,22 @@ def test_patch_tuner(tmp_path):
     e, b = compare_fields(g, o)
     assert e < 1e-11 and b < 1e-11, (e, b)
     assert np.array_equal(g.counts(), o.counts())
+
+
+def test_choices_stored_by_an_earlier_version_are_not_taken(tmp_path):
+    # a line as stored when field_tile 0 was a tile shape and 2-D Yee had no strips
+    print("[gpu-test] both tuners with a cache file of an earlier version", flush=True)
+    from tests import fixtures as F
+    wl = F.uniform_2d(n=(64, 64), patch=(16, 16), ppc=8)
+    cache = tmp_path / "tune.txt"
+    cache.write_text("pic-tune nd=2 prec=32 n=64,64,1 patch=16,16,1 np2=15 1024 3 8 256\n"
+                     "pic-patch nd=2 prec=32 n=64,64,1 profile=0 load=0 ppc=8 32 32 1 1024\n")
+    g = gpu_sim(wl, 32)
+    r = g.autotune(steps=2, cache=str(cache))
+    assert r["from_cache"] == 0 and r["trials"] > 0
+    box = W.uniform_2d(n=(64, 64), patch=(16, 16), ppc=8)
+    r = autotune_patch(box, 32, candidates=(16, 32), warm=2, steps=2, cache=str(cache))[2]
+    assert r["from_cache"] == 0 and r["trials"] > 0
+    # the choices stored now are
+    assert gpu_sim(wl, 32).autotune(steps=2, cache=str(cache))["from_cache"] == 1
+    assert autotune_patch(box, 32, candidates=(16, 32), warm=2, steps=2, cache=str(cache))[2]["from_cache"] == 1
