@@ -1586,7 +1586,7 @@ void SimImpl<T>::autotune(int steps, const char *cache, PicTuneResult *out)
     };
     Cfg best{desc.block, desc.field_tile, ls0, desc.chunk};
     double best_ms = timed(best);
-    auto try_knob = [&](int Cfg::*field, std::initializer_list<int> values) {
+    auto try_knob = [&](int Cfg::*field, const std::vector<int> &values) {
         for (int v : values) {
             if (v == best.*field) continue;
             Cfg c = best;
@@ -1600,7 +1600,13 @@ void SimImpl<T>::autotune(int steps, const char *cache, PicTuneResult *out)
     };
     try_knob(&Cfg::block, {256, 512, 1024});
     if (nd == 2) try_knob(&Cfg::field_tile, {1, 2, 3, 4, 5});
-    try_knob(&Cfg::lane_stride, {std::max(1, ls0 / 2), std::min(64, ls0 * 2), 1});
+    // half and twice the handle's stride, and 1; in 3-D also 2, 4 and 8, where
+    // lanes further apart meet fewer atomics on one address
+    std::vector<int> strides = {std::max(1, ls0 / 2), std::min(64, ls0 * 2), 1};
+    if (nd == 3)
+        for (int v : {2, 4, 8})
+            if (std::find(strides.begin(), strides.end(), v) == strides.end()) strides.push_back(v);
+    try_knob(&Cfg::lane_stride, strides);
     try_knob(&Cfg::chunk, {1024, 2048, 4096, 8192});
     apply(best);
     state_load(blob.data(), blob.size());

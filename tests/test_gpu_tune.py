@@ -51,3 +51,12 @@ def test_choices_stored_by_an_earlier_version_are_not_taken(tmp_path):
     # the choices stored now are
     assert gpu_sim(wl, 32).autotune(steps=2, cache=str(cache))["from_cache"] == 1
     assert autotune_patch(box, 32, candidates=(16, 32), warm=2, steps=2, cache=str(cache))[2]["from_cache"] == 1
+
+
+def test_tuner_tries_every_lane_stride_of_3d():
+    # the settings as they are, three workgroup sizes, strides 2, 4 and 8, four chunks
+    print("[gpu-test] tuner candidates of a 3-D box", flush=True)
+    from tests import fixtures as F
+    g = gpu_sim(F.blob_3d(n=(16, 16, 16), patch=(8, 8, 8), ppc0=2), 32)
+    r = g.autotune(steps=2)
+    assert r["trials"] >= 1 + 3 + 3 + 4 and r["lane_stride"] in (1, 2, 4, 8)
