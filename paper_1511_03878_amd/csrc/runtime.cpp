@@ -1076,8 +1076,10 @@ void SimImpl<T>::set_field(int comp, const double *h)
 // contiguous part and, chunk by chunk, convert one of their two pinned slots
 // while the other is filled (a pageable copy of the whole array through a
 // host vector, then one pass over it, took 3.1 ms for a 4096 x 1024 grid in
-// FP32 and 62 ms for 512 x 256 x 256; now 1.1 and 5.5 ms).  The stream is idle or
-// runs the work that made src.  False when there is no pinned memory.
+// FP32 and 62 ms for 512 x 256 x 256; now 1.1 and 5.5 ms).  The stream may still
+// run the work that made src; it is waited for first, since on the per-thread
+// default stream every thread here has one of its own.  False when there is no
+// pinned memory.
 constexpr int kReadThreads = 4;
 constexpr int64_t kReadSlot = 1 << 18;    // values per slot
 constexpr int64_t kReadLarge = 1 << 19;   // smaller arrays are not cut up
@@ -1090,6 +1092,7 @@ bool SimImpl<T>::read_back(const S *src, int64_t cnt, double *h)
     if (!stage.buf || !reading_events(2 * kReadThreads)) return false;
     int dev = 0;
     hipcheck(hipGetDevice(&dev), "device");
+    hipcheck(hipStreamSynchronize(stream), "sync");
     hipError_t rc[kReadThreads];
     auto part = [&](int k) {
         const int64_t lo = cnt * k / kReadThreads, hi = cnt * (k + 1) / kReadThreads;
@@ -1110,6 +1113,8 @@ bool SimImpl<T>::read_back(const S *src, int64_t cnt, double *h)
             const int64_t m = std::min(kReadSlot, hi - at);
             for (int64_t i = 0; i < m; ++i) h[at + i] = (double)slot[b][i];
         }
+        // (no copy into the slots may be in flight afterwards)
+        if (rc[k] != hipSuccess) (void)hipStreamSynchronize(stream);
     };
     std::vector<std::thread> pool;
     int started = 1;
@@ -1123,8 +1128,6 @@ bool SimImpl<T>::read_back(const S *src, int64_t cnt, double *h)
     part(0);
     for (int k = started; k < kReadThreads; ++k) part(k);
     for (auto &t : pool) t.join();
-    // (no copy into the slots may be in flight afterwards)
-    hipcheck(hipStreamSynchronize(stream), "sync");
     for (hipError_t e : rc) hipcheck(e, "read back");
     return true;
 }

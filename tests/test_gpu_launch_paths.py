@@ -349,3 +349,25 @@ def test_alone_and_beside_a_large_box_give_the_same_bits(case, precision):
                                                     *g.particles()[1], g.perm()])
     for a, b in zip(*runs):
         assert np.array_equal(a, b)
+
+
+def test_large_reads_of_work_queued_on_a_per_thread_stream():
+    # a handle on hipStreamPerThread (2): the threads that read a large array have
+    # streams of their own there, and the density they read is queued on the
+    # caller's (one crowded patch keeps its kernel running for milliseconds)
+    _announce("large reads with the per-thread default stream, 1024x1024 fp32 and fp64")
+    from paper_1511_03878_amd.sim import Sim
+    n, d, count = (1024, 1024), (0.1, 0.1), 2000000
+    # dyadic positions and weights: every sum is exact; in the last thread's part
+    x, w = [np.full(count, 8.25), np.full(count, 1000.25)], np.full(count, 2.0 ** -10)
+    ref = rho_2d([8.25], [1000.25], [count * 2.0 ** -10], -1.0, n)
+    rng = np.random.default_rng(6)
+    for precision in (32, 64):
+        g = Sim(dict(ndim=2, n=list(n), d=list(d), dt=W.cfl_dt(d), patch=[16, 16], periodic=[1, 1], q=-1.0, m=1.0),
+                precision, stream=2, torch_alloc=False)
+        g.set_particles(x, [np.zeros(count)] * 3, w)
+        for _ in range(3):
+            assert np.array_equal(g.field("rho"), ref)
+        f = rng.standard_normal(n).astype(np.float32).astype(np.float64)
+        g.set_field("Ey", f)
+        assert np.array_equal(g.field("Ey"), f)
