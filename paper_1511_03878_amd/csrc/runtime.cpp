@@ -17,7 +17,6 @@
 #include <cstring>
 #include <mutex>
 #include <numeric>
-#include <system_error>
 #include <thread>
 
 namespace pic {
@@ -63,6 +62,7 @@ struct PinnedPool {
     std::mutex m;
     std::vector<std::pair<char *, size_t>> kept;
     int handles = 0;
+    PinnedPool() { kept.reserve(kPinnedKept); }  // (a block is returned without allocating)
 };
 PinnedPool &pinned_pool()
 {
@@ -1116,18 +1116,19 @@ bool SimImpl<T>::read_back(const S *src, int64_t cnt, double *h)
         // (no copy into the slots may be in flight afterwards)
         if (rc[k] != hipSuccess) (void)hipStreamSynchronize(stream);
     };
-    std::vector<std::thread> pool;
+    std::thread pool[kReadThreads];
     int started = 1;
     for (; started < kReadThreads; ++started) {
         try {
-            pool.emplace_back(part, started);
-        } catch (const std::system_error &) {
-            break;  // no more threads: this one does the rest
+            pool[started] = std::thread(part, started);
+        } catch (const std::exception &) {
+            break;  // no more threads or memory: this one does the rest
         }
     }
     part(0);
     for (int k = started; k < kReadThreads; ++k) part(k);
-    for (auto &t : pool) t.join();
+    for (auto &t : pool)
+        if (t.joinable()) t.join();
     for (hipError_t e : rc) hipcheck(e, "read back");
     return true;
 }
