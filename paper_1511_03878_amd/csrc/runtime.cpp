@@ -2329,9 +2329,12 @@ std::vector<SimState> BatchImpl<T>::read_states()
     std::vector<SimState> out(members.size());
     const PinnedBlock b(std::max(sizeof(SimState) * out.size(), kPinnedSmall));
     SimState *to = b.buf ? (SimState *)b.buf : out.data();
-    for (size_t i = 0; i < members.size(); ++i)
-        hipcheck(hipMemcpyAsync(to + i, members[i]->st, sizeof(SimState), hipMemcpyDeviceToHost, stream), "states");
+    hipError_t rc = hipSuccess;
+    for (size_t i = 0; i < members.size() && rc == hipSuccess; ++i)
+        rc = hipMemcpyAsync(to + i, members[i]->st, sizeof(SimState), hipMemcpyDeviceToHost, stream);
+    // (no copy into the block may be in flight afterwards)
     hipcheck(hipStreamSynchronize(stream), "sync");
+    hipcheck(rc, "states");
     if (b.buf) std::copy(to, to + out.size(), out.begin());
     return out;
 }
