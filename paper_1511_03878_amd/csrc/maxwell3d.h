@@ -1,20 +1,16 @@
-// Block bodies of the 3-D field update.
-//
-// Field update of the 3-D patch-PIC step on a periodic box.  The Yee solver
-// runs as one fused kernel over blocks of nodes (yee3d_blocks, below); the
-// sixth-order solver as three passes over the nodes (one thread per node,
-// neighbours through the caches):
+// Block bodies of the 3-D field update on a periodic box: the Yee solver as
+// one fused kernel over blocks of nodes (yee3d_blocks, below) and the sixth-order
+// solver as three passes over the nodes (one thread per node, neighbours through
+// the caches):
 //   1. B^{n+1/2} = B^n - dt/2 curl E^n          (read F[n & 1], write B of F[(n+1) & 1])
-//      and the field energy of E^n, B^n per block of 256 nodes;
+//      and the field energy of E^n, B^n per tile of 256 consecutive nodes (x fastest);
 //   2. E^{n+1} = E^n + dt (curl B^{n+1/2} - J)   (write E of F[(n+1) & 1]; clear the
 //      other J buffer, which the next step deposits into);
 //   3. B^{n+1} = B^{n+1/2} - dt/2 curl E^{n+1}   (in place: a node's B reads only its
 //      own B and neighbouring E).
 // B updates take forward differences of E, E updates backward differences of B;
-// staggering as in the particle kernel.  A "tile" here is a block of 256
-// consecutive nodes (x fastest) of one simulation.  A simulation with the
-// sixth-order solver takes the same passes with the three-pair staggered
-// differences (weights 75/64, -25/384, 3/640) in place of the two-point ones.
+// staggering as in the particle kernel.  The sixth-order differences weigh the
+// three node pairs around a half point by 75/64, -25/384, 3/640.
 #pragma once
 
 #include "kernels.h"
@@ -36,27 +32,6 @@ __device__ __forceinline__ TileWalk tile_walk(int total, int b, int g)
     if (g & 7) return {b, total, g};
     const int x = b & 7;
     return {(int)((int64_t)total * x / 8) + (b >> 3), (int)((int64_t)total * (x + 1) / 8), g >> 3};
-}
-
-struct Node3 {
-    int64_t k;                // flat index
-    int64_t ip, jp, kp;       // flat index of the +1 neighbour along x, y, z
-    int64_t im, jm, km;       // flat index of the -1 neighbour along x, y, z
-};
-
-__device__ __forceinline__ Node3 node3(int64_t k, int fn0, int fn1, int fn2)
-{
-    const int i = (int)(k % fn0), j = (int)((k / fn0) % fn1), l = (int)(k / ((int64_t)fn0 * fn1));
-    const int64_t sx = 1, sy = fn0, sz = (int64_t)fn0 * fn1;
-    Node3 r;
-    r.k = k;
-    r.ip = k + (i + 1 < fn0 ? sx : -(int64_t)(fn0 - 1) * sx);
-    r.im = k + (i > 0 ? -sx : (int64_t)(fn0 - 1) * sx);
-    r.jp = k + (j + 1 < fn1 ? sy : -(int64_t)(fn1 - 1) * sy);
-    r.jm = k + (j > 0 ? -sy : (int64_t)(fn1 - 1) * sy);
-    r.kp = k + (l + 1 < fn2 ? sz : -(int64_t)(fn2 - 1) * sz);
-    r.km = k + (l > 0 ? -sz : (int64_t)(fn2 - 1) * sz);
-    return r;
 }
 
 // Sixth-order staggered difference of f along the axis with node index i of
@@ -100,7 +75,6 @@ __device__ __forceinline__ void hi3d_b_tiles(const SimDev<T> *__restrict__ sims,
         const int64_t k = (int64_t)lt * kMB + threadIdx.x;
         double esum = 0.0;
         if (k < fsize) {
-            const Node3 nd = node3(k, fn0, fn1, fn2);
             const gptr_t<const T> Ex = glb((const T *)Esrc[0]), Ey = glb((const T *)Esrc[1]),
                                   Ez = glb((const T *)Esrc[2]);
             const T ex = Ex[k], ey = Ey[k], ez = Ez[k];
@@ -109,20 +83,14 @@ __device__ __forceinline__ void hi3d_b_tiles(const SimDev<T> *__restrict__ sims,
             if (PASS == 0) {
                 esum = squares6(ex, ey, ez, bx, by, bz);
             }
-            if (S.morder == 6) {
-                const int i = (int)(k % fn0), j = (int)((k / fn0) % fn1), l = (int)(k / ((int64_t)fn0 * fn1));
-                const int64_t sy = fn0, sz = (int64_t)fn0 * fn1;
-                auto dx = [&](gptr_t<const T> f) { return d6<T>(f, k, 1, i, fn0, true); };
-                auto dy = [&](gptr_t<const T> f) { return d6<T>(f, k, sy, j, fn1, true); };
-                auto dz = [&](gptr_t<const T> f) { return d6<T>(f, k, sz, l, fn2, true); };
-                glb(Fn[3])[k] = bx - h * curl2(dy(Ez), iy, dz(Ey), iz);
-                glb(Fn[4])[k] = by - h * curl2(dz(Ex), iz, dx(Ez), ix);
-                glb(Fn[5])[k] = bz - h * curl2(dx(Ey), ix, dy(Ex), iy);
-            } else {
-                glb(Fn[3])[k] = bx - h * ((Ez[nd.jp] - ez) * iy - (Ey[nd.kp] - ey) * iz);
-                glb(Fn[4])[k] = by - h * ((Ex[nd.kp] - ex) * iz - (Ez[nd.ip] - ez) * ix);
-                glb(Fn[5])[k] = bz - h * ((Ey[nd.ip] - ey) * ix - (Ex[nd.jp] - ex) * iy);
-            }
+            const int i = (int)(k % fn0), j = (int)((k / fn0) % fn1), l = (int)(k / ((int64_t)fn0 * fn1));
+            const int64_t sy = fn0, sz = (int64_t)fn0 * fn1;
+            auto dx = [&](gptr_t<const T> f) { return d6<T>(f, k, 1, i, fn0, true); };
+            auto dy = [&](gptr_t<const T> f) { return d6<T>(f, k, sy, j, fn1, true); };
+            auto dz = [&](gptr_t<const T> f) { return d6<T>(f, k, sz, l, fn2, true); };
+            glb(Fn[3])[k] = bx - h * curl2(dy(Ez), iy, dz(Ey), iz);
+            glb(Fn[4])[k] = by - h * curl2(dz(Ex), iz, dx(Ez), ix);
+            glb(Fn[5])[k] = bz - h * curl2(dx(Ey), ix, dy(Ex), iy);
         }
         if (PASS == 0) {
 #pragma unroll
@@ -160,30 +128,16 @@ __device__ __forceinline__ void hi3d_e_tiles(const SimDev<T> *__restrict__ sims,
         const T ix = T(1) / S.d[0], iy = T(1) / S.d[1], iz = T(1) / S.d[2];
         const int64_t k = (int64_t)lt * kMB + threadIdx.x;
         if (k >= fsize) continue;
-        const Node3 nd = node3(k, fn0, fn1, fn2);
         const gptr_t<const T> Bx = glb((const T *)Fn[3]), By = glb((const T *)Fn[4]),
                               Bz = glb((const T *)Fn[5]);
-        const T bx = Bx[k], by = By[k], bz = Bz[k];
-        if (S.morder == 6) {
-            const int i = (int)(k % fn0), j = (int)((k / fn0) % fn1), l = (int)(k / ((int64_t)fn0 * fn1));
-            const int64_t sy = fn0, sz = (int64_t)fn0 * fn1;
-            auto dx = [&](gptr_t<const T> f) { return d6<T>(f, k, 1, i, fn0, false); };
-            auto dy = [&](gptr_t<const T> f) { return d6<T>(f, k, sy, j, fn1, false); };
-            auto dz = [&](gptr_t<const T> f) { return d6<T>(f, k, sz, l, fn2, false); };
-            glb(Fn[0])[k] = glb((const T *)Fc[0])[k] + dt * (curl2(dy(Bz), iy, dz(By), iz) - glb((const T *)Jc[0])[k]);
-            glb(Fn[1])[k] = glb((const T *)Fc[1])[k] + dt * (curl2(dz(Bx), iz, dx(Bz), ix) - glb((const T *)Jc[1])[k]);
-            glb(Fn[2])[k] = glb((const T *)Fc[2])[k] + dt * (curl2(dx(By), ix, dy(Bx), iy) - glb((const T *)Jc[2])[k]);
-            glb(Jn[0])[k] = T(0);
-            glb(Jn[1])[k] = T(0);
-            glb(Jn[2])[k] = T(0);
-            continue;
-        }
-        glb(Fn[0])[k] = glb((const T *)Fc[0])[k] +
-                        dt * ((bz - Bz[nd.jm]) * iy - (by - By[nd.km]) * iz - glb((const T *)Jc[0])[k]);
-        glb(Fn[1])[k] = glb((const T *)Fc[1])[k] +
-                        dt * ((bx - Bx[nd.km]) * iz - (bz - Bz[nd.im]) * ix - glb((const T *)Jc[1])[k]);
-        glb(Fn[2])[k] = glb((const T *)Fc[2])[k] +
-                        dt * ((by - By[nd.im]) * ix - (bx - Bx[nd.jm]) * iy - glb((const T *)Jc[2])[k]);
+        const int i = (int)(k % fn0), j = (int)((k / fn0) % fn1), l = (int)(k / ((int64_t)fn0 * fn1));
+        const int64_t sy = fn0, sz = (int64_t)fn0 * fn1;
+        auto dx = [&](gptr_t<const T> f) { return d6<T>(f, k, 1, i, fn0, false); };
+        auto dy = [&](gptr_t<const T> f) { return d6<T>(f, k, sy, j, fn1, false); };
+        auto dz = [&](gptr_t<const T> f) { return d6<T>(f, k, sz, l, fn2, false); };
+        glb(Fn[0])[k] = glb((const T *)Fc[0])[k] + dt * (curl2(dy(Bz), iy, dz(By), iz) - glb((const T *)Jc[0])[k]);
+        glb(Fn[1])[k] = glb((const T *)Fc[1])[k] + dt * (curl2(dz(Bx), iz, dx(Bz), ix) - glb((const T *)Jc[1])[k]);
+        glb(Fn[2])[k] = glb((const T *)Fc[2])[k] + dt * (curl2(dx(By), ix, dy(Bx), iy) - glb((const T *)Jc[2])[k]);
         glb(Jn[0])[k] = T(0);
         glb(Jn[1])[k] = T(0);
         glb(Jn[2])[k] = T(0);
