@@ -39,6 +39,10 @@
  *  - Host pointers are borrowed for the duration of the call only.  Device
  *    memory is owned by the handle and obtained through the allocator hook
  *    given at creation (NULL: hipMalloc / hipFree).
+ *  - Host resources: calls that return device data pass it through pinned host
+ *    memory.  Up to two such blocks of at most 32 MB each are kept for the next
+ *    call of any handle and freed with the last handle.  pic_fields_get of 2^19
+ *    nodes or more starts three threads, which end with the call.
  *  - All device work of a handle is ordered on the HIP stream given at
  *    creation (NULL: the default stream).  Handles are not thread-safe.
  */

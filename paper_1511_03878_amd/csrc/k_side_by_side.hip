@@ -2,8 +2,10 @@
 // the first workgroups take the field strips or tiles, the others a pass of the
 // re-binning (the two share no data).  On two streams the fork and the join
 // cost about 7 us per step, as much as the passes of a small box themselves
-// (128 x 128 box: field update 6 us, re-binning 20 us); here they cost nothing.  Yee: one launch with the count pass; sixth order: its three
-// passes go with the count, check and scatter passes.
+// (128 x 128 box: field update 6 us and the three launches of the re-binning 20 us
+// by themselves, 18 us together here); here they cost nothing.  Yee: one launch
+// with the count pass; sixth order: its three passes go with the count, check and
+// scatter passes.
 #include <algorithm>
 
 #include "kernels.h"

@@ -2066,7 +2066,12 @@ void BatchImpl<T>::build_tables()
     // eighth above an equal part of the mean occupied patch: a chunk that the
     // mean divides exactly leaves half of the patches a rest of a few
     // particles (512 x 512 box of 1024-particle patches: 91.5 us per step at
-    // a chunk of 1024, 88.2 us with whole patches).
+    // a chunk of 1024, 88.2 us with whole patches).  The lower bound is that of
+    // 2-D; in 3-D, whose tiles are larger, two items per patch measure faster
+    // than the four it gives small boxes (us per step at chunks of 1024, this
+    // rule's, 1536, 2304, 4608, 9216: 64 x 48 x 40 box of 4600-particle patches
+    // 158 / 150 / 147 / 132 / 149 / 178, 96 x 64 x 64 FP64 in 8 x 8 x 4 patches
+    // 436 / 400 / 413 / 406 / 392 / 436).
     chunk = 0;
     for (auto *m : members) chunk = std::max(chunk, (int)m->desc.chunk);
     if (chunk == 0) {
@@ -2113,7 +2118,13 @@ void BatchImpl<T>::build_tables()
     // 512 x 256 95 / 79, 1536 x 384 laser box 92.0 / 87.5, 64 x 48 x 40 154.7 /
     // 153.0, 96 x 64 x 64 400 / 401; 1024 x 1024 box 436 / 451, scan of 16
     // 361 / 383, 256 x 128 x 128 2285 / 2350, where the re-binning's passes lose
-    // occupancy to the field update's registers or wait for it).
+    // occupancy to the field update's registers or wait for it).  Near the two
+    // limits the sides are within 2 %.  2048 patches: 512 x 512 in 1024 patches
+    // 93.5 / 90.9, 720 x 720 in 2025 149.1 / 152.4, 768 x 768 in 2304 159.6 /
+    // 162.1, 512 x 256 in 2048 88.0 / 89.7; in 3-D 48 x 48 x 56 in 2016 204.3 /
+    // 203.4, 64 x 48 x 64 in 3072 235.8 / 239.7.  3 * 2^18 nodes: 864 x 896
+    // 208.5 / 207.9, 896 x 896 212.2 / 209.6, FP64 288.6 / 291.1 and 316.9 / 317.9;
+    // 128 x 96 x 64 533.9 / 522.2, 128 x 96 x 72 563.8 / 562.5.
     side_by_side = !(yee_any && hi_order) && tile_preset == 0 && total_patches <= 2048 && nodes <= kSideBySideNodes;
     if (std::getenv("PIC_LOG"))
         std::fprintf(stderr,
